@@ -103,16 +103,54 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   return (uint16_t)(u >> 16);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+// One step of a 64-lane butterfly: the value of lane l ^ 32 or l ^ 16 by a
+// permlane swap (both operands v: afterwards the two registers hold the lower
+// and the upper partner of every pair), and, once lanes 8 (4) apart hold the
+// same value, of lane l ^ 8 .. l ^ 1 by a DPP read.  All of them are VALU
+// instructions; a ds_bpermute per step waits for an LDS round trip each
+// (measured on the 16 sums per wave of a K-means pass: see kmeans_pass_kernel).
+__device__ __forceinline__ float2 lanes_x32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float2 lanes_x16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float v) {
+  const int x = (int)__float_as_uint(v);
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false));
+}
+constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppX2 = 0x4E, kDppX1 = 0xB1;
+
+// Sum over the 16 lanes of a DPP row, in every lane (order 8, 4, 2, 1).
+__device__ __forceinline__ float row16_sum(float v) {
+  v += lane_dpp<kDppRor8>(v);
+  v += lane_dpp<kDppRor4>(v);
+  v += lane_dpp<kDppX2>(v);
+  v += lane_dpp<kDppX1>(v);
   return v;
 }
 
+// Sum over the wave in every lane: the butterfly 32, 16, 8, 4, 2, 1.
+__device__ __forceinline__ float wave_sum(float v) {
+  float2 p = lanes_x32(v);
+  v = p.x + p.y;
+  p = lanes_x16(v);
+  v = p.x + p.y;
+  return row16_sum(v);
+}
+
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  float2 p = lanes_x32(v);
+  v = fmaxf(p.x, p.y);
+  p = lanes_x16(v);
+  v = fmaxf(p.x, p.y);
+  v = fmaxf(v, lane_dpp<kDppRor8>(v));
+  v = fmaxf(v, lane_dpp<kDppRor4>(v));
+  v = fmaxf(v, lane_dpp<kDppX2>(v));
+  return fmaxf(v, lane_dpp<kDppX1>(v));
 }
 
 __device__ __forceinline__ int wave_sum_int(int v) {

@@ -15,15 +15,14 @@
 //                  fp32 accumulation; anchors staged in LDS per 64-dimension
 //                  chunk) scaled by the two inverse norms; fp32: grid
 //                  (ceil(n/4), G), a wave-per-row FMA loop.
-//   kmeans         grid G x (512|256): Lloyd passes; each wave keeps every
-//                  centroid's slice of dimensions in registers, processes
-//                  rows round-robin, and the per-wave partial sums are
-//                  combined in LDS in fixed wave order (deterministic).
-//   score_final    grid G x (512|256): cluster means of unit rows per tapped
-//                  layer (same fixed-order reduction), cluster mean of m, and
-//                  the factored score of every non-anchor row.
+//   kmeans         grid (NB, G) x 512 per Lloyd pass: rows and centroids in
+//                  LDS, distances, then per-block cluster sums in a fixed
+//                  order (deterministic).
+//   score_final    cluster means of unit rows per tapped layer (same
+//                  fixed-order sums), cluster mean of m, and the factored
+//                  score of every non-anchor row.
 //
-// Lane-to-dimension map used by kmeans/score_final: lane l owns VPL
+// Lane-to-dimension map of the dot products and distances: lane l owns VPL
 // dimensions, in chunks of 8: dims {c*512 + 8*l + e : c < VPL/8, e < 8}.
 #include <algorithm>
 #include <cfloat>
@@ -440,222 +439,316 @@ __global__ void __launch_bounds__(256) anchor_maxsim_f32_kernel(
 }
 
 // ------------------------------------------------------------- clustering
-// Multi-workgroup Lloyd iterations.  Each tile's m non-anchor rows are split
-// into NB contiguous row ranges, one 256-thread block per range.  One Lloyd
-// pass = kmeans_assign (assign rows to the nearest centroid, per-block
-// per-cluster partial sums) + kmeans_update (fixed-order sum of the NB
-// partials, new centroids in place; empty clusters keep theirs).  The host
-// enqueues max_iter passes; once a pass changes no assignment, update sets a
-// per-tile flag and the remaining launches return at once.  Centroids live
-// in global memory and are staged in LDS; every reduction runs in a fixed
-// order, so results are bitwise reproducible.
+// Lloyd iterations.  Each tile's m non-anchor rows are split into NB
+// contiguous row ranges, one 512-thread block per range and pass.  The host
+// enqueues max_iter passes; the passes after the first that changes no
+// assignment return at once.
+//
+// A pass (kmeans_pass_kernel): the block's rows go to LDS by DMA (at most
+// kRowLdsBytes at a time), the centroids into LDS beside them; each wave takes
+// 4 rows at a time against 4 centroids, whose 16 sums over the dimensions are
+// reduced together (reduce_4x4); then every thread owns 2 or 4 dimensions and
+// adds the rows from LDS to their clusters.  Sums run in a fixed order, the
+// same whatever the number of tiles: row j of the block's range belongs to
+// lane group j % 4, each group adds its rows in ascending order, and the groups
+// are added ((0 + 1) + 2) + 3.
+//
+// Centroids of pass p > 0: the NB blocks' partial sums added in block order,
+// divided by the count; an empty cluster keeps its centroid.  Up to
+// kSelfUpdateBlocks blocks every block forms them itself from the partial sums
+// (which alternate between two buffers), more blocks read what
+// kmeans_update_kernel wrote between the passes: reading NB * K * d floats per
+// block costs less than a launch only while few blocks do it.
+//
+// What bounds it: latency.  One tile of 576 x 1024 bf16 patches has 16 blocks
+// and ten passes of which 3 or 4 work; 19 launches (pass and update) took
+// 180 us, ten take 51 us (20 tiles: 171 -> 75 us).
+constexpr int kClusterThreads = 512;
+constexpr int kRowLdsBytes = 64 << 10;
+constexpr int kMaxRowsPerBlock = 128;
+constexpr int kSelfUpdateBlocks = 512;
 
-// Per-cluster partial sums over this block's rows [j0, j1) of layer `l`
-// (optionally scaled by w[i]): out[k*d + c] for k < K.  The block makes one
-// pass per cluster over its rows (they stay in L1/L2), one wave per row; the 4
-// wave partials are combined in a fixed order through LDS, 512 dimensions at
-// a time (red: 4 * 512 floats).
-template <typename FT, int VPL>
-__device__ inline void block_cluster_sums(const FeatArgs& fa, int l, int g, int d, int K,
-                                          const int32_t* U, int j0, int j1, const int32_t* lab,
-                                          const float* w, float* red, float* out) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int k = 0; k < K; ++k) {
-    float acc[VPL];
+struct ClusterWs {
+  float* cent;      // [G][K][d]
+  float* psum;      // [G][NB][K][d] (kmeans; two such buffers with self-update) / [G][NB][L][K][d] (means)
+  int32_t* pcnt;    // [G][NB][K]       rows per cluster; kmeans: bit 16 of the first = an assignment changed
+  float* pm;        // [G][NB][K]       partial sums of m (kmeans with self-update: the second pcnt)
+  int32_t* conv;    // [G]
+  int32_t* assign;  // [G][n]  assignment of non-anchor row j (index into U)
+  float* mu;        // [G][L][K][d] (kmeans with self-update: the second cent)
+  float* mbar;      // [G][K]
+  int NB, RB;       // blocks per tile, rows per block
+  int nb_used;
+  int64_t psum2;    // elements from the first to the second partial-sum buffer
+};
+constexpr int kChangedBit = 1 << 16;
+
+// Rows staged at a time: a multiple of 4 (at least 8: a row has at most 8 KB).
+__host__ __device__ inline int chunk_rows(int rb, int row_bytes) {
+  const int fit = kRowLdsBytes / row_bytes / 4 * 4, need = (rb + 3) / 4 * 4;
+  return fit < need ? fit : need;
+}
+
+// LDS bytes of the staged rows (the DMA writes whole KBs).
+__host__ __device__ inline int chunk_bytes(int rb, int row_bytes) {
+  const int ch = chunk_rows(rb, row_bytes), rows = ch < rb ? ch : rb;
+  return (rows * row_bytes + 1023) / 1024 * 1024;
+}
+
+// Rows sidx[0..nr) of layer l into LDS at byte offset `lds`, packed at d elements.
+template <typename FT>
+__device__ __forceinline__ void stage_rows(const FeatArgs& fa, int l, int g, int d, const int* sidx, int nr,
+                                           uint32_t lds) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  constexpr int E = 16 / (int)sizeof(FT);
+  const int per_row = d / E, total = nr * per_row;  // 16-byte pieces
+  for (int base = wave * 64; base < total; base += kClusterThreads) {
+    const int p = min(base + lane, total - 1);
+    const int r = p / per_row, c = p - r * per_row;
+    dma16(reinterpret_cast<const uint16_t*>(feat_row<FT>(fa, l, g, sidx[r]) + c * E), lds + base * 16);
+  }
+}
+
+// 16 values v[4 r + k] per lane summed over the wave: lane row rho (16 lanes)
+// ends with the sums of r = rho, for k = 0..3 in v[0..3].  The butterfly of
+// wave_sum (same pairs in the same order, so the same bits), halving the number
+// of values at its first two steps instead of repeating them for each.
+__device__ __forceinline__ void reduce_4x4(float (&v)[16]) {
 #pragma unroll
-    for (int v = 0; v < VPL; ++v) acc[v] = 0.f;
-    for (int j = j0 + wave; j < j1; j += 4) {
-      if (lab[j - j0] != k) continue;
-      const int i = U[j];
-      float x[VPL];
-      load_slice<FT, VPL>(feat_row<FT>(fa, l, g, i), d, lane, x);
-      const float sc = w ? w[i] : 1.0f;
+  for (int i = 0; i < 8; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
+    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
 #pragma unroll
-      for (int v = 0; v < VPL; ++v) acc[v] = fmaf(x[v], sc, acc[v]);
-    }
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 4]), false, false);
+    v[i] = row16_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+  }
+}
+
+// Dimensions per thread of the row sums (512 threads).
+template <int NCH>
+constexpr int kDims = NCH <= 2 ? 2 : 4;
+
+// Adds the nr staged rows to acc[row % 4][cluster][this thread's dimensions]
+// (first dimension DP * threadIdx.x); sc: the rows' scales, null for 1.
+template <typename FT, int KM, int DP>
+__device__ __forceinline__ void add_rows(float (&acc)[4][KM][DP], const uint8_t* rows, int d, int nr, const int* lab,
+                                         const float* sc) {
+  const int dim = DP * threadIdx.x;
+  if (dim >= d) return;
+  for (int q = 0; q < nr; q += 4) {
 #pragma unroll
-    for (int q = 0; q < VPL / 8; ++q) {
+    for (int v = 0; v < 4; ++v) {
+      if (q + v >= nr) break;
+      const FT* src = reinterpret_cast<const FT*>(rows) + (q + v) * d + dim;
+      float x[DP];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) red[wave * 512 + lane * 8 + e] = acc[8 * q + e];
-      __syncthreads();
-      for (int c = threadIdx.x; c < 512; c += blockDim.x) {
-        const int dim = q * 512 + c;
-        if (dim < d) out[k * d + dim] = ((red[c] + red[512 + c]) + red[1024 + c]) + red[1536 + c];
-      }
-      __syncthreads();
+      for (int e = 0; e < DP; ++e) x[e] = Feat<FT>::load1(src + e);
+      const int k = __builtin_amdgcn_readfirstlane(lab[q + v]);
+      const float w = sc ? sc[q + v] : 1.0f;
+#pragma unroll
+      for (int c = 0; c < KM; ++c)
+#pragma unroll
+        for (int e = 0; e < DP; ++e) {
+          const float t = fmaf(x[e], w, acc[v][c][e]);
+          acc[v][c][e] = k == c ? t : acc[v][c][e];
+        }
     }
   }
 }
 
-// Fixed-order combine of the 4 waves' per-cluster sums acc[k] (k < K) into
-// out[k*d + c], 512 dimensions at a time through LDS (red: 4 * 512 floats).
-template <int KM, int VPL>
-__device__ __forceinline__ void block_combine_cluster_sums(const float (&acc)[KM][VPL], int K, int d, float* red,
-                                                           float* out) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+template <int KM, int DP>
+__device__ __forceinline__ void store_sums(const float (&acc)[4][KM][DP], int K, int d, float* out) {
+  const int dim = DP * threadIdx.x;
+  if (dim >= d) return;
 #pragma unroll
   for (int k = 0; k < KM; ++k) {
     if (k >= K) break;
 #pragma unroll
-    for (int q = 0; q < VPL / 8; ++q) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) red[wave * 512 + lane * 8 + e] = acc[k][8 * q + e];
-      __syncthreads();
-      for (int c = threadIdx.x; c < 512; c += blockDim.x) {
-        const int dim = q * 512 + c;
-        if (dim < d) out[k * d + dim] = ((red[c] + red[512 + c]) + red[1024 + c]) + red[1536 + c];
-      }
-      __syncthreads();
-    }
+    for (int e = 0; e < DP; ++e)
+      out[k * d + dim + e] = ((acc[0][k][e] + acc[1][k][e]) + acc[2][k][e]) + acc[3][k][e];
   }
 }
 
-// Adds row x (scaled by sc) to the accumulator of its cluster.  fmaf(x, 1, a)
-// rounds like a + x, and each cluster receives its rows in increasing row
-// order, the order block_cluster_sums uses: both paths give the same bits.
-// (Written as per-element selects: a branch per cluster gets merged by the
-// compiler into one dynamically indexed update, which lives in scratch.)
-template <int KM, int VPL>
-__device__ __forceinline__ void add_to_cluster(float (&acc)[KM][VPL], int k_row, const float* x, float sc) {
-#pragma unroll
-  for (int k = 0; k < KM; ++k) {
-    const bool mine = k_row == k;
-#pragma unroll
-    for (int v = 0; v < VPL; ++v) {
-      const float t = fmaf(x[v], sc, acc[k][v]);
-      acc[k][v] = mine ? t : acc[k][v];
-    }
-  }
-}
-
-// Cluster counts up to this size keep one accumulator per cluster in
-// registers and read every row once per pass.
-constexpr int kFusedClusters = 4;
-
-constexpr int kMaxRowsPerBlock = 128;
-
-struct ClusterWs {
-  float* cent;      // [G][K][d]
-  float* psum;      // [G][NB][K][d]    (kmeans) / [G][NB][L][K][d] (means)
-  int32_t* pcnt;    // [G][NB][K]
-  float* pm;        // [G][NB][K]       partial sums of m
-  int32_t* pchg;    // [G][NB]
-  int32_t* conv;    // [G]
-  int32_t* assign;  // [G][n]  assignment of non-anchor row j (index into U)
-  float* mu;        // [G][L][K][d]
-  float* mbar;      // [G][K]
-  int NB, RB;       // blocks per tile, rows per block
-};
-
-template <typename FT, int VPL>
-__global__ void __launch_bounds__(256) kmeans_assign_kernel(int n, int d, int n_anchor, int K,
-                                                            int first, FeatArgs fa, int last,
-                                                            const int32_t* __restrict__ rest_list,
-                                                            ClusterWs cw, int32_t* __restrict__ cluster_out) {
-  extern __shared__ __attribute__((aligned(16))) float smem[];  // 16-byte centroid reads
-  float* cs = smem;                 // [K*d] centroids
-  float* red = cs + K * d;          // [4*512]
-  __shared__ int lab[kMaxRowsPerBlock];
-  __shared__ int sidx[kMaxRowsPerBlock];  // U[j0..j1): one dependent load less per row
+template <typename FT, int NCH, int KM>
+__global__ void __launch_bounds__(kClusterThreads) kmeans_pass_kernel(int n, int d, int n_anchor, int K, int pass,
+                                                                      int self, FeatArgs fa, int last,
+                                                                      const int32_t* __restrict__ rest_list,
+                                                                      ClusterWs cw, int32_t* __restrict__ cluster_out) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];  // staged rows, then centroids [K][d]
+  __shared__ int lab[kMaxRowsPerBlock], old[kMaxRowsPerBlock], sidx[kMaxRowsPerBlock];
+  __shared__ int scnt[8];
   __shared__ int chg;
   const int g = blockIdx.y, b = blockIdx.x;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int m = n - n_anchor;
-  const int j0 = b * cw.RB, j1 = min(m, j0 + cw.RB);
-  if (j0 >= j1 || cw.conv[g]) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int j0 = b * cw.RB, j1 = min(m, j0 + cw.RB), nr = j1 - j0;
+  const int64_t slot = (int64_t)g * cw.NB + b;
+  // buffers of this pass and of the one before (the same without self-update)
+  const bool odd = self && (pass & 1);
+  int32_t* cnt_cur = odd ? reinterpret_cast<int32_t*>(cw.pm) : cw.pcnt;
+  const int32_t* cnt_prev = self && !odd ? reinterpret_cast<const int32_t*>(cw.pm) : cw.pcnt;
+  float* cent_cur = (odd ? cw.mu : cw.cent) + (int64_t)g * K * d;
+  const float* cent_prev = (self && !odd ? cw.mu : cw.cent) + (int64_t)g * K * d;
+  float* sum_cur = cw.psum + (odd ? cw.psum2 : 0) + slot * K * d;
+  const float* sum_prev = cw.psum + (self && !odd ? cw.psum2 : 0) + (int64_t)g * cw.NB * K * d;
+  if (self && pass > 0) {
+    // converged: the pass before changed nothing (NB <= 32 blocks, one lane each)
+    const int c = lane < cw.nb_used ? cnt_prev[((int64_t)g * cw.NB + lane) * K] : 0;
+    if (!__ballot(c & kChangedBit)) {
+      if (tid == 0) cnt_cur[slot * K] = 0;  // for the next pass, which reads this buffer
+      return;
+    }
+  } else if (!self && cw.conv[g]) {
+    return;
+  }
   const int32_t* U = rest_list + (int64_t)g * n;
-  for (int j = j0 + threadIdx.x; j < j1; j += blockDim.x) sidx[j - j0] = U[j];
-  float* cent = cw.cent + (int64_t)g * K * d;
-  if (first) {
+  int32_t* asg = cw.assign + (int64_t)g * n;
+  for (int j = tid; j < nr; j += kClusterThreads) {
+    sidx[j] = U[j0 + j];
+    old[j] = pass > 0 ? asg[j0 + j] : -1;
+  }
+  if (tid == 0) chg = 0;
+  if (self && pass > 0 && wave < K) {
+    // rows of cluster `wave` over all blocks
+    const int c = wave_sum_int(lane < cw.nb_used ? (cnt_prev[((int64_t)g * cw.NB + lane) * K + wave] & 0xFFFF) : 0);
+    if (lane == 0) scnt[wave] = c;
+  }
+  __syncthreads();
+  const int row_bytes = d * (int)sizeof(FT);
+  const int CH = chunk_rows(cw.RB, row_bytes);
+  const uint32_t lds = lds_offset(smem);
+  stage_rows<FT>(fa, last, g, d, sidx, min(CH, nr), lds);
+  float* cs = reinterpret_cast<float*>(smem + chunk_bytes(cw.RB, row_bytes));
+  if (pass == 0) {
     // centroids at rows floor(k*m/K) of the non-anchor list
-    for (int t = threadIdx.x; t < K * d; t += blockDim.x) {
+    for (int t = tid * 8; t < K * d; t += kClusterThreads * 8) {
       const int k = t / d, c = t - k * d;
-      const FT* row = feat_row<FT>(fa, last, g, U[(int)(((int64_t)k * m) / K)]);
-      const float v = Feat<FT>::load1(row + c);
-      cs[t] = v;
-      if (b == 0) cent[t] = v;
+      float x[8];
+      Feat<FT>::load8(feat_row<FT>(fa, last, g, U[(int)(((int64_t)k * m) / K)]) + c, x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) cs[t + e] = x[e];
+      if (b == 0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) cent_cur[t + e] = x[e];
+      }
+    }
+  } else if (self) {
+    for (int t = tid * 4; t < K * d; t += kClusterThreads * 4) {
+      const int c = scnt[t / d];
+      float4 v;
+      if (c > 0) {
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int b0 = 0; b0 < cw.nb_used; b0 += 8) {
+          float4 x[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (b0 + u < cw.nb_used) x[u] = *reinterpret_cast<const float4*>(sum_prev + (int64_t)(b0 + u) * K * d + t);
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (b0 + u < cw.nb_used) {
+              s.x += x[u].x;
+              s.y += x[u].y;
+              s.z += x[u].z;
+              s.w += x[u].w;
+            }
+        }
+        const float fc = (float)c;
+        v = make_float4(__fdiv_rn(s.x, fc), __fdiv_rn(s.y, fc), __fdiv_rn(s.z, fc), __fdiv_rn(s.w, fc));
+      } else {
+        v = *reinterpret_cast<const float4*>(cent_prev + t);
+      }
+      *reinterpret_cast<float4*>(cs + t) = v;
+      if (b == 0) *reinterpret_cast<float4*>(cent_cur + t) = v;
     }
   } else {
-    for (int t = threadIdx.x; t < K * d; t += blockDim.x) cs[t] = cent[t];
+    for (int t = tid * 4; t < K * d; t += kClusterThreads * 4)
+      *reinterpret_cast<float4*>(cs + t) = *reinterpret_cast<const float4*>(cent_prev + t);
   }
-  if (threadIdx.x == 0) chg = first;
-  __syncthreads();
-  int32_t* asg = cw.assign + (int64_t)g * n;
-  const bool fused = K <= kFusedClusters;
-  float acc[kFusedClusters][VPL];
+  constexpr int DP = kDims<NCH>;
+  float acc[4][KM][DP];
 #pragma unroll
-  for (int k = 0; k < kFusedClusters; ++k)
+  for (int v = 0; v < 4; ++v)
 #pragma unroll
-    for (int v = 0; v < VPL; ++v) acc[k][v] = 0.f;
-  // d % 8 == 0: every 8-dimension chunk of a lane is whole, and its centroid
-  // values are read as two 16-byte LDS vectors (lane l reads bytes 32 l ..,
-  // no bank conflicts; scalar reads at 8-float lane strides conflict 8 ways).
-  // Same terms in the same order as the scalar loop, so the same bits.
-  const bool d8 = (d & 7) == 0;
-  for (int j = j0 + wave; j < j1; j += 4) {
-    float x[VPL];
-    load_slice<FT, VPL>(feat_row<FT>(fa, last, g, sidx[j - j0]), d, lane, x);
-    int best = 0;
-    float bd = 0.f;
-    for (int k = 0; k < K; ++k) {
-      float s = 0.f;
-      if (d8) {
+    for (int k = 0; k < KM; ++k)
 #pragma unroll
-        for (int c = 0; c < VPL / 8; ++c) {
+      for (int e = 0; e < DP; ++e) acc[v][k][e] = 0.f;
+  for (int c0 = 0; c0 < nr; c0 += CH) {
+    const int cn = min(CH, nr - c0);
+    if (c0 > 0) {
+      __syncthreads();  // the chunk before is summed
+      stage_rows<FT>(fa, last, g, d, sidx + c0, cn, lds);
+    }
+    dma_wait_all();
+    __syncthreads();
+    const FT* rows = reinterpret_cast<const FT*>(smem);
+    for (int r0 = wave; r0 < cn; r0 += 32) {  // rows r0, r0 + 8, r0 + 16, r0 + 24
+      float bd = 0.f;
+      int best = 0;
+#pragma unroll
+      for (int kb = 0; kb < KM; kb += 4) {
+        if (kb >= K) break;
+        float s[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s[q] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
           const int base = c * 512 + lane * 8;
           if (base < d) {
-            const float4 c0 = *reinterpret_cast<const float4*>(cs + k * d + base);
-            const float4 c1 = *reinterpret_cast<const float4*>(cs + k * d + base + 4);
-            const float cc[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+            float x[4][8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const float t = x[8 * c + e] - cc[e];
-              s = fmaf(t, t, s);
+            for (int r = 0; r < 4; ++r) Feat<FT>::load8(rows + min(r0 + 8 * r, cn - 1) * d + base, x[r]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              if (kb + k >= K) break;
+              float cc[8];
+              Feat<float>::load8(cs + (kb + k) * d + base, cc);
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                  const float t = x[r][e] - cc[e];
+                  s[4 * r + k] = fmaf(t, t, s[4 * r + k]);
+                }
             }
           }
         }
-      } else {
+        reduce_4x4(s);
 #pragma unroll
-        for (int v = 0; v < VPL; ++v) {
-          const int dim = slice_dim(v, lane);
-          const float t = dim < d ? x[v] - cs[k * d + dim] : 0.f;
-          s = fmaf(t, t, s);
-        }
+        for (int k = 0; k < 4; ++k)
+          if (kb + k < K && (kb + k == 0 || s[k] < bd)) {
+            bd = s[k];
+            best = kb + k;
+          }
       }
-      s = wave_sum(s);
-      if (k == 0 || s < bd) {
-        bd = s;
-        best = k;
+      const int r = r0 + 8 * (lane >> 4);
+      if ((lane & 15) == 0 && r < cn) {
+        lab[c0 + r] = best;
+        if (old[c0 + r] != best) chg = 1;
+        asg[j0 + c0 + r] = best;
+        cluster_out[(int64_t)g * n + sidx[c0 + r]] = best;
       }
     }
-    if (fused) add_to_cluster<kFusedClusters, VPL>(acc, best, x, 1.0f);
-    if (lane == 0) {
-      if (!first && asg[j] != best) chg = 1;
-      asg[j] = best;
-      lab[j - j0] = best;
-      cluster_out[(int64_t)g * n + sidx[j - j0]] = best;
+    __syncthreads();
+    add_rows<FT, KM, DP>(acc, smem, d, cn, lab + c0, nullptr);
+  }
+  store_sums<KM, DP>(acc, K, d, sum_cur);
+  if (wave == 0) {
+    for (int k = 0; k < K; ++k) {
+      int c = 0;
+      for (int q = 0; q < nr; q += 64) c += __popcll(__ballot(q + lane < nr && lab[min(q + lane, nr - 1)] == k));
+      if (lane == 0) cnt_cur[slot * K + k] = c | (k == 0 && chg ? kChangedBit : 0);
     }
   }
-  __syncthreads();
-  const int64_t slot = (int64_t)g * cw.NB + b;
-  if (fused)
-    block_combine_cluster_sums<kFusedClusters, VPL>(acc, K, d, red, cw.psum + slot * K * d);
-  else
-    block_cluster_sums<FT, VPL>(fa, last, g, d, K, U, j0, j1, lab, nullptr, red, cw.psum + slot * K * d);
-  if (threadIdx.x < K) {
-    int c = 0;
-    for (int j = j0; j < j1; ++j) c += lab[j - j0] == (int)threadIdx.x;
-    cw.pcnt[slot * K + threadIdx.x] = c;
-  }
-  if (threadIdx.x == 0) cw.pchg[slot] = chg;
 }
 
 // grid (ceil(K*d/256), G): new centroids = fixed-order sums of the partials.
-__global__ void __launch_bounds__(256) kmeans_update_kernel(int d, int K, ClusterWs cw, int nb_used) {
+__global__ void __launch_bounds__(256) kmeans_update_kernel(int d, int K, ClusterWs cw) {
   const int g = blockIdx.y;
   if (cw.conv[g]) return;
   int any = 0;
-  for (int b = 0; b < nb_used; ++b) any |= cw.pchg[(int64_t)g * cw.NB + b];
+  for (int b = 0; b < cw.nb_used; ++b) any |= cw.pcnt[((int64_t)g * cw.NB + b) * K] & kChangedBit;
   if (!any) {
     if (blockIdx.x == 0 && threadIdx.x == 0) cw.conv[g] = 1;
     return;
@@ -665,77 +758,74 @@ __global__ void __launch_bounds__(256) kmeans_update_kernel(int d, int K, Cluste
   const int k = t / d;
   float s = 0.f;
   int c = 0;
-  for (int b = 0; b < nb_used; ++b) {
+  for (int b = 0; b < cw.nb_used; ++b) {
     const int64_t slot = (int64_t)g * cw.NB + b;
     s += cw.psum[slot * K * d + t];
-    c += cw.pcnt[slot * K + k];
+    c += cw.pcnt[slot * K + k] & 0xFFFF;
   }
   if (c > 0) cw.cent[(int64_t)g * K * d + t] = __fdiv_rn(s, (float)c);
 }
 
-// Partial per-cluster sums of unit rows (every tapped layer) and of m.
-template <typename FT, int VPL>
-__global__ void __launch_bounds__(256) cluster_sum_kernel(int n, int d, int n_anchor, int K,
-                                                          int n_layers, FeatArgs fa,
-                                                          const float* __restrict__ nu,
-                                                          const int32_t* __restrict__ rest_list,
-                                                          const float* __restrict__ mvec, ClusterWs cw) {
-  __shared__ float red[4 * 512];
-  __shared__ int lab[kMaxRowsPerBlock];
-  __shared__ int sidx[kMaxRowsPerBlock];  // U[j0..j1), then m of those rows: no dependent
-  __shared__ float sm_m[kMaxRowsPerBlock];  // index loads inside the row loops
-  const int g = blockIdx.y, b = blockIdx.x;
+// Partial per-cluster sums of unit rows, a tapped layer per blockIdx.z, and of
+// m.  The rows are staged and summed as in a K-means pass.
+template <typename FT, int NCH, int KM>
+__global__ void __launch_bounds__(kClusterThreads) cluster_sum_kernel(int n, int d, int n_anchor, int K, int n_layers,
+                                                                      FeatArgs fa, const float* __restrict__ nu,
+                                                                      const int32_t* __restrict__ rest_list,
+                                                                      const float* __restrict__ mvec, ClusterWs cw) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];  // staged rows
+  __shared__ int lab[kMaxRowsPerBlock], sidx[kMaxRowsPerBlock];
+  __shared__ float sc[kMaxRowsPerBlock], sm_m[kMaxRowsPerBlock];
+  const int g = blockIdx.y, b = blockIdx.x, l = blockIdx.z;
+  const int tid = threadIdx.x;
   const int m = n - n_anchor;
-  const int j0 = b * cw.RB, j1 = min(m, j0 + cw.RB);
-  if (j0 >= j1) return;
+  const int j0 = b * cw.RB, j1 = min(m, j0 + cw.RB), nr = j1 - j0;
   const int32_t* U = rest_list + (int64_t)g * n;
-  const int32_t* asg = cw.assign + (int64_t)g * n;
-  for (int j = j0 + threadIdx.x; j < j1; j += blockDim.x) {
-    lab[j - j0] = asg[j];
-    const int i = U[j];
-    sidx[j - j0] = i;
-    sm_m[j - j0] = mvec[(int64_t)g * n + i];
+  const float* nul = nu + ((int64_t)g * n_layers + l) * n;
+  for (int j = tid; j < nr; j += kClusterThreads) {
+    const int i = U[j0 + j];
+    sidx[j] = i;
+    lab[j] = cw.assign[(int64_t)g * n + j0 + j];
+    sc[j] = nul[i];
+    sm_m[j] = mvec[(int64_t)g * n + i];
   }
   __syncthreads();
-  const int64_t slot = (int64_t)g * cw.NB + b;
-  for (int l = 0; l < n_layers; ++l) {
-    const float* nul = nu + ((int64_t)g * n_layers + l) * n;
-    float* out = cw.psum + (slot * n_layers + l) * K * d;
-    if (K <= kFusedClusters) {
-      // one read of every row: each goes to its cluster's accumulator
-      const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-      float acc[kFusedClusters][VPL];
+  constexpr int DP = kDims<NCH>;
+  float acc[4][KM][DP];
 #pragma unroll
-      for (int k = 0; k < kFusedClusters; ++k)
+  for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int v = 0; v < VPL; ++v) acc[k][v] = 0.f;
-      for (int j = j0 + wave; j < j1; j += 4) {
-        const int i = sidx[j - j0];
-        float x[VPL];
-        load_slice<FT, VPL>(feat_row<FT>(fa, l, g, i), d, lane, x);
-        add_to_cluster<kFusedClusters, VPL>(acc, lab[j - j0], x, nul[i]);
-      }
-      block_combine_cluster_sums<kFusedClusters, VPL>(acc, K, d, red, out);
-    } else {
-      block_cluster_sums<FT, VPL>(fa, l, g, d, K, U, j0, j1, lab, nul, red, out);
-    }
+    for (int k = 0; k < KM; ++k)
+#pragma unroll
+      for (int e = 0; e < DP; ++e) acc[v][k][e] = 0.f;
+  const int CH = chunk_rows(cw.RB, d * (int)sizeof(FT));
+  const uint32_t lds = lds_offset(smem);
+  for (int c0 = 0; c0 < nr; c0 += CH) {
+    const int cn = min(CH, nr - c0);
+    if (c0 > 0) __syncthreads();
+    stage_rows<FT>(fa, l, g, d, sidx + c0, cn, lds);
+    dma_wait_all();
+    __syncthreads();
+    add_rows<FT, KM, DP>(acc, smem, d, cn, lab + c0, sc + c0);
   }
-  if (threadIdx.x < K) {
+  const int64_t slot = (int64_t)g * cw.NB + b;
+  store_sums<KM, DP>(acc, K, d, cw.psum + (slot * n_layers + l) * K * d);
+  if (l == 0 && tid >= kClusterThreads - 64 && tid - (kClusterThreads - 64) < K) {
+    const int k = tid - (kClusterThreads - 64);
     int c = 0;
     float sm = 0.f;
-    for (int j = j0; j < j1; ++j)
-      if (lab[j - j0] == (int)threadIdx.x) {
+    for (int j = 0; j < nr; ++j)
+      if (lab[j] == k) {
         ++c;
-        sm += sm_m[j - j0];
+        sm += sm_m[j];
       }
-    cw.pcnt[slot * K + threadIdx.x] = c;
-    cw.pm[slot * K + threadIdx.x] = sm;
+    cw.pcnt[slot * K + k] = c;
+    cw.pm[slot * K + k] = sm;
   }
 }
 
 // grid (ceil(L*K*d/256), G): mu = fixed-order sums / counts; mbar likewise.
-__global__ void __launch_bounds__(256) cluster_mean_kernel(int d, int K, int n_layers, ClusterWs cw,
-                                                           int nb_used) {
+__global__ void __launch_bounds__(256) cluster_mean_kernel(int d, int K, int n_layers, ClusterWs cw) {
   const int g = blockIdx.y;
   const int t = blockIdx.x * 256 + threadIdx.x;
   const int per = K * d;
@@ -743,10 +833,21 @@ __global__ void __launch_bounds__(256) cluster_mean_kernel(int d, int K, int n_l
     const int l = t / per, r = t - l * per, k = r / d;
     float s = 0.f;
     int c = 0;
-    for (int b = 0; b < nb_used; ++b) {
-      const int64_t slot = (int64_t)g * cw.NB + b;
-      s += cw.psum[(slot * n_layers + l) * per + r];
-      c += cw.pcnt[slot * K + k];
+    for (int b0 = 0; b0 < cw.nb_used; b0 += 8) {
+      float x[8];
+      int y[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int64_t slot = (int64_t)g * cw.NB + min(b0 + u, cw.nb_used - 1);
+        x[u] = cw.psum[(slot * n_layers + l) * per + r];
+        y[u] = cw.pcnt[slot * K + k];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (b0 + u < cw.nb_used) {
+          s += x[u];
+          c += y[u];
+        }
     }
     cw.mu[((int64_t)g * n_layers + l) * per + r] = c ? __fdiv_rn(s, (float)c) : 0.f;
   }
@@ -754,7 +855,7 @@ __global__ void __launch_bounds__(256) cluster_mean_kernel(int d, int K, int n_l
     const int k = threadIdx.x;
     float s = 0.f;
     int c = 0;
-    for (int b = 0; b < nb_used; ++b) {
+    for (int b = 0; b < cw.nb_used; ++b) {
       const int64_t slot = (int64_t)g * cw.NB + b;
       s += cw.pm[slot * K + k];
       c += cw.pcnt[slot * K + k];
@@ -798,7 +899,7 @@ __global__ void __launch_bounds__(256) score_rows_wave_kernel(int n, int d, int 
   if (lane == 0) s_out[(int64_t)g * n + i] = s + mvec[(int64_t)g * n + i] + cw.mbar[(int64_t)g * K + k];
 }
 
-// The same scores, 64 rows per block and 16 per wave in batches of RB rows
+// The same scores, 64 or 16 rows per block, a quarter per wave in batches of RB rows
 // whose feature loads (two tapped layers at a time) are all issued before
 // any is used; the tile's cluster means mu[l][k] (n_layers * K * d floats, at
 // most kMuLdsFloats) are staged in LDS once per block.  Per row and layer a
@@ -813,7 +914,8 @@ __global__ void __launch_bounds__(256) score_rows_kernel(int n, int d, int n_anc
                                                          FeatArgs fa, const float* __restrict__ nu,
                                                          const int32_t* __restrict__ rest_list,
                                                          const float* __restrict__ mvec, ClusterWs cw,
-                                                         float* __restrict__ s_out, float* __restrict__ m_out) {
+                                                         float* __restrict__ s_out, float* __restrict__ m_out,
+                                                         int rows_per_wave) {
   __shared__ __attribute__((aligned(16))) float smu[kMuLdsFloats];
   const int g = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -830,8 +932,8 @@ __global__ void __launch_bounds__(256) score_rows_kernel(int n, int d, int n_anc
   constexpr int NCH = VPL / 8;
   const int32_t* U = rest_list + (int64_t)g * n;
   const int32_t* asg = cw.assign + (int64_t)g * n;
-  const int jw = blockIdx.x * kScoreRowsPerBlock + 16 * wave;
-  for (int jb = 0; jb < 16; jb += RB) {
+  const int jw = (blockIdx.x * 4 + wave) * rows_per_wave;
+  for (int jb = 0; jb < rows_per_wave; jb += RB) {
     if (jw + jb >= m) break;
     int ii[RB], kc[RB];
 #pragma unroll
@@ -924,7 +1026,7 @@ size_t score_ws_layout(int G, int n, int d, int n_layers, int K, ScoreWs* w, cha
   char* p_psum = take((size_t)G * NB * L1 * K * d * 4);
   char* p_pcnt = take((size_t)G * NB * K * 4);
   char* p_pm = take((size_t)G * NB * K * 4);
-  char* p_pchg = take((size_t)G * NB * 4);
+  take((size_t)G * NB * 4);  // holds nothing now: the workspace keeps its size
   char* p_conv = take((size_t)G * 4);
   char* p_asg = take((size_t)G * n * 4);
   char* p_mu = take((size_t)G * L1 * K * d * 4);
@@ -938,7 +1040,6 @@ size_t score_ws_layout(int G, int n, int d, int n_layers, int K, ScoreWs* w, cha
     w->cw.psum = reinterpret_cast<float*>(p_psum);
     w->cw.pcnt = reinterpret_cast<int32_t*>(p_pcnt);
     w->cw.pm = reinterpret_cast<float*>(p_pm);
-    w->cw.pchg = reinterpret_cast<int32_t*>(p_pchg);
     w->cw.conv = reinterpret_cast<int32_t*>(p_conv);
     w->cw.assign = reinterpret_cast<int32_t*>(p_asg);
     w->cw.mu = reinterpret_cast<float*>(p_mu);
@@ -948,7 +1049,8 @@ size_t score_ws_layout(int G, int n, int d, int n_layers, int K, ScoreWs* w, cha
   return off;
 }
 
-template <typename FT, int VPL>
+// NCH = chunks of 512 dimensions of a row (1, 2, 4); KM = 4 or 8 clusters.
+template <typename FT, int NCH, int KM>
 hipError_t launch_cluster_kernels(int G, int n, int d, int n_anchor, int K, int max_iter,
                                   int n_layers, const FeatArgs& fa, ScoreWs ws,
                                   int32_t* cluster_out, float* s_out, float* m_out, hipStream_t st) {
@@ -956,18 +1058,22 @@ hipError_t launch_cluster_kernels(int G, int n, int d, int n_anchor, int K, int 
   const int NB = ws.cw.NB;
   ws.cw.RB = m > 0 ? (m + NB - 1) / NB : 1;
   const int nb_used = m > 0 ? (m + ws.cw.RB - 1) / ws.cw.RB : 0;
+  ws.cw.nb_used = nb_used;
+  ws.cw.psum2 = (int64_t)G * NB * K * d;
   // NB >= ceil(n / kMaxRowsPerBlock) guarantees these; checked before any launch
-  if (ws.cw.RB > kMaxRowsPerBlock || nb_used > NB) return hipErrorInvalidValue;
+  if (ws.cw.RB > kMaxRowsPerBlock || nb_used > NB || NB > 64) return hipErrorInvalidValue;
+  const size_t rows_lds = chunk_bytes(ws.cw.RB, d * (int)sizeof(FT));
   if (m > 0) {
     ProfScope ps(KC_KMEANS, st);
-    const size_t sh = ((size_t)K * d + 4 * 512) * 4;
+    // the second partial-sum buffer is the second layer's part of psum
+    const bool self = n_layers >= 2 && G * nb_used <= kSelfUpdateBlocks;
     for (int it = 0; it < max_iter; ++it) {
-      kmeans_assign_kernel<FT, VPL><<<dim3(nb_used, G), 256, sh, st>>>(
-          n, d, n_anchor, K, it == 0, fa, n_layers - 1, ws.rest, ws.cw, cluster_out);
+      kmeans_pass_kernel<FT, NCH, KM><<<dim3(nb_used, G), kClusterThreads, rows_lds + (size_t)K * d * 4, st>>>(
+          n, d, n_anchor, K, it, self, fa, n_layers - 1, ws.rest, ws.cw, cluster_out);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
-      if (it + 1 < max_iter) {
-        kmeans_update_kernel<<<dim3(ceil_div(K * d, 256), G), 256, 0, st>>>(d, K, ws.cw, nb_used);
+      if (!self && it + 1 < max_iter) {
+        kmeans_update_kernel<<<dim3(ceil_div(K * d, 256), G), 256, 0, st>>>(d, K, ws.cw);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
@@ -976,19 +1082,21 @@ hipError_t launch_cluster_kernels(int G, int n, int d, int n_anchor, int K, int 
   {
     ProfScope ps(KC_SCORE_FINAL, st);
     if (m > 0) {
-      cluster_sum_kernel<FT, VPL><<<dim3(nb_used, G), 256, 0, st>>>(
+      cluster_sum_kernel<FT, NCH, KM><<<dim3(nb_used, G, n_layers), kClusterThreads, rows_lds, st>>>(
           n, d, n_anchor, K, n_layers, fa, ws.nu, ws.rest, ws.mvec, ws.cw);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
-      cluster_mean_kernel<<<dim3(ceil_div(n_layers * K * d, 256), G), 256, 0, st>>>(d, K, n_layers,
-                                                                                  ws.cw, nb_used);
+      cluster_mean_kernel<<<dim3(ceil_div(n_layers * K * d, 256), G), 256, 0, st>>>(d, K, n_layers, ws.cw);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    if ((int64_t)n_layers * K * d <= kMuLdsFloats)
-      score_rows_kernel<FT, VPL><<<dim3(std::max(1, ceil_div(m, kScoreRowsPerBlock)), G), 256, 0, st>>>(
-          n, d, n_anchor, K, n_layers, fa, ws.nu, ws.rest, ws.mvec, ws.cw, s_out, m_out);
-    else
+    constexpr int VPL = 8 * NCH;
+    if ((int64_t)n_layers * K * d <= kMuLdsFloats) {
+      // 16 rows per block while 64 would leave most CUs without one
+      const int rpb = (int64_t)ceil_div(std::max(m, 1), kScoreRowsPerBlock) * G >= 256 ? kScoreRowsPerBlock : 16;
+      score_rows_kernel<FT, VPL><<<dim3(std::max(1, ceil_div(m, rpb)), G), 256, 0, st>>>(
+          n, d, n_anchor, K, n_layers, fa, ws.nu, ws.rest, ws.mvec, ws.cw, s_out, m_out, rpb / 4);
+    } else
       score_rows_wave_kernel<FT, VPL><<<dim3(std::max(1, ceil_div(m, 4)), G), 256, 0, st>>>(
           n, d, n_anchor, K, n_layers, fa, ws.nu, ws.rest, ws.mvec, ws.cw, s_out, m_out);
     return hipGetLastError();
@@ -999,11 +1107,12 @@ template <typename FT>
 hipError_t dispatch_cluster(int G, int n, int d, int n_anchor, int K, int max_iter, int n_layers,
                             const FeatArgs& fa, const ScoreWs& ws, int32_t* cl, float* s,
                             float* mo, hipStream_t st) {
-  if (d <= 512)
-    return launch_cluster_kernels<FT, 8>(G, n, d, n_anchor, K, max_iter, n_layers, fa, ws, cl, s, mo, st);
-  if (d <= 1024)
-    return launch_cluster_kernels<FT, 16>(G, n, d, n_anchor, K, max_iter, n_layers, fa, ws, cl, s, mo, st);
-  return launch_cluster_kernels<FT, 32>(G, n, d, n_anchor, K, max_iter, n_layers, fa, ws, cl, s, mo, st);
+#define SPIDER_CLUSTER(NCH_, KM_) \
+  launch_cluster_kernels<FT, NCH_, KM_>(G, n, d, n_anchor, K, max_iter, n_layers, fa, ws, cl, s, mo, st)
+  if (d <= 512) return K <= 4 ? SPIDER_CLUSTER(1, 4) : SPIDER_CLUSTER(1, 8);
+  if (d <= 1024) return K <= 4 ? SPIDER_CLUSTER(2, 4) : SPIDER_CLUSTER(2, 8);
+  return SPIDER_CLUSTER(4, 4);  // K <= 4 past 1024 dimensions
+#undef SPIDER_CLUSTER
 }
 
 }  // namespace
