@@ -53,11 +53,47 @@ __global__ void __launch_bounds__(256) proj_rows_kernel(int G, int tps, int cap,
   }
 }
 
+constexpr int kProjSplitMax = 4;
+
+// Columns 4 t .. 4 t + 3 (t = threadIdx.x + 256 j, grid (rows, slices of 1024
+// columns)) of the sum of a row's split-K partials in split order, plus the
+// bias: every load of the row in flight at once.
+__device__ __forceinline__ float4 proj_sum(const float* P, int split, int64_t pstride, int64_t at, const float* b,
+                                           int c) {
+  float4 x[kProjSplitMax];
+#pragma unroll
+  for (int s = 0; s < kProjSplitMax; ++s)
+    if (s < split) x[s] = *reinterpret_cast<const float4*>(P + s * pstride + at);
+  const float4 bb = b ? make_float4(b[c], b[c + 1], b[c + 2], b[c + 3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 v = make_float4(0.f + x[0].x, 0.f + x[0].y, 0.f + x[0].z, 0.f + x[0].w);  // no -0
+#pragma unroll
+  for (int s = 1; s < kProjSplitMax; ++s)
+    if (s < split) {
+      v.x += x[s].x;
+      v.y += x[s].y;
+      v.z += x[s].z;
+      v.w += x[s].w;
+    }
+  if (b) v = make_float4(v.x + bb.x, v.y + bb.y, v.z + bb.z, v.w + bb.w);
+  return v;
+}
+
+// d % 4 == 0 takes proj_sum's pieces, other widths (fp32 only) a column at a time.
 template <typename AT>
 __global__ void __launch_bounds__(256) proj_hidden_kernel(int d, const float* __restrict__ P, int split,
                                                           int64_t pstride, const float* __restrict__ b,
                                                           AT* __restrict__ h) {
   const int64_t m = blockIdx.x;
+  if (d % 4 == 0) {
+    const int c = 4 * (blockIdx.y * 256 + threadIdx.x);
+    if (c >= d) return;
+    const float4 v = proj_sum(P, split, pstride, m * d + c, b, c);
+    const float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ProjAct<AT>::store(h + m * d + c + q, gelu_erf(e[q]));
+    return;
+  }
+  if (blockIdx.y > 0) return;
   for (int c = threadIdx.x; c < d; c += 256) {
     float v = 0.f;
     for (int s = 0; s < split; ++s) v += P[s * pstride + m * d + c];
@@ -73,6 +109,16 @@ __global__ void __launch_bounds__(256) proj_out_kernel(int d, const float* __res
   const int64_t m = blockIdx.x;
   const int r = dst[m];
   if (r < 0) return;
+  if (d % 4 == 0) {
+    const int c = 4 * (blockIdx.y * 256 + threadIdx.x);
+    if (c >= d) return;
+    const float4 v = proj_sum(P, split, pstride, m * d + c, b, c);
+    const float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ProjAct<AT>::store(y + (int64_t)r * d + c + q, e[q]);
+    return;
+  }
+  if (blockIdx.y > 0) return;
   for (int c = threadIdx.x; c < d; c += 256) {
     float v = 0.f;
     for (int s = 0; s < split; ++s) v += P[s * pstride + m * d + c];
@@ -80,8 +126,6 @@ __global__ void __launch_bounds__(256) proj_out_kernel(int d, const float* __res
     ProjAct<AT>::store(y + (int64_t)r * d + c, v);
   }
 }
-
-constexpr int kProjSplitMax = 4;
 
 struct ProjWs {
   int32_t *src, *dst;
@@ -127,7 +171,7 @@ spider_status run_projector(int G, int tps, int cap, const int32_t* idx, const i
   g1.g[0] = GemmGroup{feats, ws.src, M, w1, nullptr, d_hid, ws.P1, d_hid, (int64_t)M * d_hid, 0, 0, 0};
   hipError_t e = bf16 ? launch_gemm_bf16(g1, kProjSplitMax, st) : launch_gemm_f32(g1, kProjSplitMax, st);
   SPIDER_REQUIRE(e == hipSuccess, SPIDER_ERR_HIP, "projector gemm 1: %s", hipGetErrorString(e));
-  proj_hidden_kernel<AT><<<M, 256, 0, st>>>(d_hid, ws.P1, g1.split, (int64_t)M * d_hid, b1,
+  proj_hidden_kernel<AT><<<dim3(M, ceil_div(d_hid, 1024)), 256, 0, st>>>(d_hid, ws.P1, g1.split, (int64_t)M * d_hid, b1,
                                             reinterpret_cast<AT*>(ws.h));
   SPIDER_LAUNCHED("proj_hidden");
   GemmArgs g2{};
@@ -138,7 +182,7 @@ spider_status run_projector(int G, int tps, int cap, const int32_t* idx, const i
   g2.g[0] = GemmGroup{ws.h, nullptr, M, w2, nullptr, d_out, ws.P2, d_out, (int64_t)M * d_out, 0, 0, 0};
   e = bf16 ? launch_gemm_bf16(g2, kProjSplitMax, st) : launch_gemm_f32(g2, kProjSplitMax, st);
   SPIDER_REQUIRE(e == hipSuccess, SPIDER_ERR_HIP, "projector gemm 2: %s", hipGetErrorString(e));
-  proj_out_kernel<AT><<<M, 256, 0, st>>>(d_out, ws.P2, g2.split, (int64_t)M * d_out, b2, ws.dst,
+  proj_out_kernel<AT><<<dim3(M, ceil_div(d_out, 1024)), 256, 0, st>>>(d_out, ws.P2, g2.split, (int64_t)M * d_out, b2, ws.dst,
                                          reinterpret_cast<AT*>(x_out));
   SPIDER_LAUNCHED("proj_out");
   return SPIDER_OK;
