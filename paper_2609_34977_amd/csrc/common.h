@@ -154,9 +154,14 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 __device__ __forceinline__ int wave_sum_int(int v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = (int)(p[0] + p[1]);
+  const auto q = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = (int)(q[0] + q[1]);
+  v += __builtin_amdgcn_update_dpp(v, v, kDppRor8, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(v, v, kDppRor4, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(v, v, kDppX2, 0xF, 0xF, false);
+  return v + __builtin_amdgcn_update_dpp(v, v, kDppX1, 0xF, 0xF, false);
 }
 
 // Order-preserving map of a float to uint32 (-0.0 is mapped like +0.0).

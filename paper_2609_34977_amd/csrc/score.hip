@@ -7,9 +7,9 @@
 // Kernels (all per tile g, enqueued in this order):
 //   score_prep     grid (ceil(n/16), G) x 256: a_i (sequential fp32 head sum,
 //                  then one IEEE division) and 1/|F^l_i| for every tapped layer.
-//   anchor_topk    grid G x 1024: LDS bitonic sort of 64-bit keys
-//                  (~order(a), i); the first n_anchor are the anchors; block
-//                  scans write the ascending anchor and non-anchor lists.
+//   anchor_topk    grid G x 64: one wave finds the n_anchor-th largest score
+//                  bit by bit and writes the ascending anchor and non-anchor
+//                  lists.
 //   anchor_maxsim  m_i = max_p u_i . u_p.  bf16: grid (ceil(n/128), G) x 256,
 //                  v_mfma_f32_32x32x16_bf16 on the raw rows (exact products,
 //                  fp32 accumulation; anchors staged in LDS per 64-dimension
@@ -30,6 +30,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "topk.h"
 
 namespace spider {
 namespace {
@@ -210,103 +211,46 @@ void launch_score_prep(int G, int n, int H, int d, int n_layers, const float* at
 // ------------------------------------------------------------- anchor_topk
 constexpr int kMaxN = 4096;
 
-__device__ inline void block_bitonic_sort(uint64_t* keys, int N) {
-  for (int k = 2; k <= N; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = threadIdx.x; t < N / 2; t += blockDim.x) {
-        const int i = (t / j) * 2 * j + (t % j);
-        const int p = i + j;
-        const bool up = (i & k) == 0;
-        const uint64_t x = keys[i], y = keys[p];
-        if ((x > y) == up) {
-          keys[i] = y;
-          keys[p] = x;
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// Exclusive scan of flags[0..n) (values 0/1) into pos[], returns the total.
-// Uses `scratch` (>= blockDim/64 + 1 ints of LDS).
-template <typename IT>
-__device__ inline int block_scan_flags(const IT* flags, IT* pos, int n, int* scratch) {
-  // each thread handles a contiguous chunk
-  const int T = blockDim.x;
-  const int per = (n + T - 1) / T;
-  const int beg = threadIdx.x * per;
-  const int end = min(n, beg + per);
-  int local = 0;
-  for (int i = beg; i < end; ++i) local += flags[i];
-  // inclusive scan across the block of `local`
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int v = local;
+// One wave per tile: the n_anchor largest scores (ties to the lower index),
+// then the ascending anchor and non-anchor lists from ballots.
+template <int NV>
+__global__ void __launch_bounds__(64) anchor_topk_kernel(int n, int n_anchor, const float* __restrict__ a,
+                                                         int32_t* __restrict__ cluster_out, float* __restrict__ s_out,
+                                                         int32_t* __restrict__ anc_list,
+                                                         int32_t* __restrict__ rest_list, int32_t* __restrict__ conv) {
+  const int g = blockIdx.x, lane = threadIdx.x;
+  if (lane == 0) conv[g] = 0;
+  const int64_t o = (int64_t)g * n;
+  const int nv = (n + 63) / 64;
+  uint32_t key[NV];
+  {
+    float x[NV];  // every load first: a load under its own bounds check waits for the one before it
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(v, o, 64);
-    if (lane >= o) v += u;
+    for (int v = 0; v < NV; ++v) x[v] = a[o + min(64 * v + lane, n - 1)];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) key[v] = 64 * v + lane < n ? float_order_key(x[v]) : 0u;
   }
-  if (lane == 63) scratch[wave] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int w = 0; w < T / 64; ++w) {
-      const int t = scratch[w];
-      scratch[w] = run;
-      run += t;
-    }
-    scratch[T / 64] = run;
-  }
-  __syncthreads();
-  int run = scratch[wave] + v - local;
-  for (int i = beg; i < end; ++i) {
-    pos[i] = (IT)run;
-    run += flags[i];
-  }
-  const int total = scratch[T / 64];
-  __syncthreads();
-  return total;
-}
-
-__global__ void __launch_bounds__(1024) anchor_topk_kernel(int n, int n_anchor,
-                                                           const float* __restrict__ a,
-                                                           int32_t* __restrict__ cluster_out,
-                                                           float* __restrict__ s_out,
-                                                           int32_t* __restrict__ anc_list,
-                                                           int32_t* __restrict__ rest_list,
-                                                           int32_t* __restrict__ conv) {
-  __shared__ uint64_t keys[kMaxN];
-  __shared__ uint16_t flag[kMaxN];
-  __shared__ uint16_t pos[kMaxN];
-  __shared__ int scratch[17];
-  const int g = blockIdx.x;
-  if (threadIdx.x == 0) conv[g] = 0;
-  int N = 1;
-  while (N < n) N <<= 1;
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    uint64_t k = ~0ull;
-    if (i < n) k = ((uint64_t)(~float_order_key(a[(int64_t)g * n + i])) << 32) | (uint32_t)i;
-    keys[i] = k;
-  }
-  __syncthreads();
-  block_bitonic_sort(keys, N);
-  for (int p = threadIdx.x; p < n; p += blockDim.x)
-    flag[(int)(keys[p] & 0xFFFFFFFFu)] = (uint16_t)(p < n_anchor);
-  __syncthreads();
-  const int na = block_scan_flags(flag, pos, n, scratch);
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const int64_t o = (int64_t)g * n;
-    if (flag[i]) {
-      anc_list[o + pos[i]] = i;
+  const TopK<NV> top = wave_kth_largest<NV>(key, nv, n_anchor);
+  int na = 0, ties = 0;  // anchors and ties below register v
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    if (v >= nv) break;
+    const int i = 64 * v + lane;
+    const uint64_t eq = __ballot(i < n && key[v] == top.t);
+    const bool sel = i < n && (key[v] > top.t || (key[v] == top.t && ties + lanes_below(eq) < top.ties));
+    const uint64_t m = __ballot(sel);
+    const int before = na + lanes_below(m);
+    if (sel) {
+      anc_list[o + before] = i;
       cluster_out[o + i] = -1;
       s_out[o + i] = INFINITY;
-    } else {
-      rest_list[o + (i - pos[i])] = i;
+    } else if (i < n) {
+      rest_list[o + (i - before)] = i;
       cluster_out[o + i] = 0;
     }
+    ties += __popcll(eq);
+    na += __popcll(m);
   }
-  (void)na;
 }
 
 // ------------------------------------------------------------- anchor_maxsim
@@ -321,7 +265,31 @@ __global__ void __launch_bounds__(1024) anchor_topk_kernel(int n, int n_anchor,
 // covers k in [k0 + 32 hi, k0 + 32 hi + 32) as 4 chunks of 8 for both
 // operands (v_mfma_f32_32x32x16_bf16, exact products, fp32 accumulation in
 // chunk order), then acc * nu_row * nu_anchor, maxed.
+// Accumulator register r of an anchor tile: anchor p0 + 8 (r / 4) + 4 hi + r % 4
+// against the lane's row.  The anchors' inverse norms are loaded all at once (a
+// load under its own bounds check waits for the one before it: 16 times two
+// dependent loads per tile).
+__device__ __forceinline__ float max_over_anchors(const floatx16& acc, int p0, int hi, int n_anchor,
+                                                  const int32_t* anc, const float* nu_g, float nu_r, float best) {
+  int at[16];
+  float nu[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) at[r] = anc[min(p0 + 8 * (r >> 2) + 4 * hi + (r & 3), n_anchor - 1)];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) nu[r] = nu_g[at[r]];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float v = acc[r] * nu_r * nu[r];
+    best = p0 + 8 * (r >> 2) + 4 * hi + (r & 3) < n_anchor ? fmaxf(best, v) : best;
+  }
+  return best;
+}
+
 constexpr int kMaxAnchorTiles = 8;
+// Up to two 128-row blocks per CU the 32-row kernel is faster (64 tiles of 576,
+// 320 such blocks: 69 against 80 us); from there on the anchors it reads once
+// per 32 rows instead of once per 128 cost more (256 tiles: 243 against 218 us).
+constexpr int kMaxsimBlocks = 512;
 
 __global__ void __launch_bounds__(256) anchor_maxsim_bf16_kernel(
     int n, int d, int n_anchor, FeatArgs fa, int last, const float* __restrict__ nu_last,
@@ -404,16 +372,92 @@ __global__ void __launch_bounds__(256) anchor_maxsim_bf16_kernel(
     // acc[j][r]: anchor 32 (t0 + j) + 8 (r / 4) + 4 hi + r % 4, data row my_row
 #pragma unroll
     for (int j = 0; j < kMaxAnchorTiles; ++j)
-      if (j < nt) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int pa = 32 * (t0 + j) + 8 * (r >> 2) + 4 * hi + (r & 3);
-          if (pa < n_anchor) best = fmaxf(best, acc[j][r] * nu_r * nu_g[anc[pa]]);
-        }
-      }
+      if (j < nt) best = max_over_anchors(acc[j], 32 * (t0 + j), hi, n_anchor, anc, nu_g, nu_r, best);
   }
   best = fmaxf(best, __shfl_xor(best, 32, 64));
   if (hi == 0 && row_ok) mvec[(int64_t)g * n + my_row] = n_anchor > 0 ? best : 0.f;
+}
+
+// The same similarities where 128-row blocks would leave most CUs idle: a block
+// per 32 rows, a wave per anchor tile (4 tiles per pass over the rows).  Rows
+// and anchors of a 64-dimension chunk go to LDS by DMA into a ring of four
+// stages, three chunks ahead (row r's 16-byte chunk c at slot c ^ ((r >> 1) & 7)
+// as in the kernel above).  Same MFMAs in the same order, and a maximum does
+// not depend on its order: the same bits.  Bounded by the latency of the
+// chunks; one tile of 576 x 1024 with 89 anchors: 5 blocks took 31 us, 18 take
+// 11 us; 20 tiles with 201 anchors 49 -> 26 us.
+__global__ void __launch_bounds__(256) anchor_maxsim_bf16_rows32_kernel(
+    int n, int d, int n_anchor, FeatArgs fa, int last, const float* __restrict__ nu_last,
+    int64_t nu_stride_g, const int32_t* __restrict__ anc_list, float* __restrict__ mvec) {
+  constexpr int STAGES = 4, LEAD = STAGES - 1, STAGE = 5 * 4096, PER_IT = 5;  // rows, then 4 anchor tiles
+  __shared__ __attribute__((aligned(1024))) uint8_t ring[STAGES * STAGE];
+  const int g = blockIdx.y;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, hi = lane >> 5,
+            lo = lane & 31;
+  const int i0 = blockIdx.x * 32, my_row = i0 + lo;
+  const uint32_t lds = lds_offset(ring);
+  const float* nu_g = nu_last + (int64_t)g * nu_stride_g;
+  const int32_t* anc = anc_list + (int64_t)g * n;
+  const float nu_r = my_row < n ? nu_g[my_row] : 0.f;
+  const int n_at = (n_anchor + 31) / 32, nkc = (d + 63) / 64;
+  // DMA: lane l fills slot l % 8 of row 8 q + l / 8 of a 32-row tile; this wave
+  // brings rows 8 wave .. of the row tile and its own anchor tile
+  const int dr = lane >> 3, dc = lane & 7;
+  const int r_row = 8 * wave + dr, r_ch = 8 * (dc ^ ((r_row >> 1) & 7));
+  const uint16_t* rp = feat_row<uint16_t>(fa, last, g, min(i0 + r_row, n - 1));
+  float best = -INFINITY;
+  for (int t0 = 0; t0 < n_at; t0 += 4) {
+    const int t = min(t0 + wave, n_at - 1);  // a repeated tile changes no maximum
+    const uint16_t* ap[4];
+    int a_ch[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = 8 * q + dr;
+      ap[q] = feat_row<uint16_t>(fa, last, g, anc[min(32 * t + r, n_anchor - 1)]);
+      a_ch[q] = 8 * (dc ^ ((r >> 1) & 7));
+    }
+    auto issue = [&](int kc, auto S) {
+      const uint32_t st = lds + decltype(S)::value * STAGE;
+      // past the last dimension: any element of the row (its products are dropped below)
+      auto at = [&](int ch) { return 64 * kc + ch < d ? 64 * kc + ch : 0; };
+      dma16(rp + at(r_ch), st + wave * 1024);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) dma16(ap[q] + at(a_ch[q]), st + 4096 * (1 + wave) + q * 1024);
+    };
+    floatx16 acc{};
+    __syncthreads();  // the pass before is done with the ring
+    static_for<0, LEAD>([&](auto P) { issue(min((int)P.value, nkc - 1), P); });
+    dma_wait_barrier<(LEAD - 1) * PER_IT>();
+    for (int k0 = 0; k0 < nkc; k0 += STAGES) {
+      static_for<0, STAGES>([&](auto P) {
+        const int kc = k0 + P.value;
+        if (kc < nkc) {
+          issue(min(kc + LEAD, nkc - 1), std::integral_constant<int, (P.value + LEAD) % STAGES>{});
+          const uint8_t* st = ring + P.value * STAGE;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const int at = lo * 128 + 16 * ((4 * hi + c) ^ ((lo >> 1) & 7));
+            u32x4 bv = *reinterpret_cast<const u32x4*>(st + at);
+            u32x4 av = *reinterpret_cast<const u32x4*>(st + 4096 * (1 + wave) + at);
+            if (64 * kc + 32 * hi + 8 * c >= d) av = bv = u32x4{0, 0, 0, 0};
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av),
+                                                          __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
+          }
+          dma_wait_barrier<(LEAD - 1) * PER_IT>();
+        }
+      });
+    }
+    dma_wait_all();
+    best = max_over_anchors(acc, 32 * t, hi, n_anchor, anc, nu_g, nu_r, best);
+  }
+  best = fmaxf(best, __shfl_xor(best, 32, 64));
+  __syncthreads();
+  float* wbest = reinterpret_cast<float*>(ring);  // [4][32]
+  if (hi == 0) wbest[32 * wave + lo] = best;
+  __syncthreads();
+  if (wave == 0 && hi == 0 && my_row < n)
+    mvec[(int64_t)g * n + my_row] =
+        n_anchor > 0 ? fmaxf(fmaxf(wbest[lo], wbest[32 + lo]), fmaxf(wbest[64 + lo], wbest[96 + lo])) : 0.f;
 }
 
 // fp32 features: one wave per data row, loop over anchors.
@@ -458,11 +502,12 @@ __global__ void __launch_bounds__(256) anchor_maxsim_f32_kernel(
 // kSelfUpdateBlocks blocks every block forms them itself from the partial sums
 // (which alternate between two buffers), more blocks read what
 // kmeans_update_kernel wrote between the passes: reading NB * K * d floats per
-// block costs less than a launch only while few blocks do it.
+// block costs less than a launch only while few blocks do it (20 tiles, 320
+// blocks: 94 us against 113; 64 tiles alike; 256 tiles: 484 against 416).
 //
 // What bounds it: latency.  One tile of 576 x 1024 bf16 patches has 16 blocks
 // and ten passes of which 3 or 4 work; 19 launches (pass and update) took
-// 180 us, ten take 51 us (20 tiles: 171 -> 75 us).
+// 180 us, ten take 62 us (20 tiles: 171 -> 82 us).
 constexpr int kClusterThreads = 512;
 constexpr int kRowLdsBytes = 64 << 10;
 constexpr int kMaxRowsPerBlock = 128;
@@ -593,28 +638,31 @@ __global__ void __launch_bounds__(kClusterThreads) kmeans_pass_kernel(int n, int
   const float* cent_prev = (self && !odd ? cw.mu : cw.cent) + (int64_t)g * K * d;
   float* sum_cur = cw.psum + (odd ? cw.psum2 : 0) + slot * K * d;
   const float* sum_prev = cw.psum + (self && !odd ? cw.psum2 : 0) + (int64_t)g * cw.NB * K * d;
+  const int32_t* U = rest_list + (int64_t)g * n;
+  int32_t* asg = cw.assign + (int64_t)g * n;
+  // nothing below waits for the convergence flags but the exit itself: the
+  // loads of a pass form one chain of two (indices, rows), not of four
+  const int u_j = U[j0 + min(tid, nr - 1)];
+  const int a_j = pass > 0 ? asg[j0 + min(tid, nr - 1)] : -1;
   if (self && pass > 0) {
-    // converged: the pass before changed nothing (NB <= 32 blocks, one lane each)
-    const int c = lane < cw.nb_used ? cnt_prev[((int64_t)g * cw.NB + lane) * K] : 0;
+    const int32_t* cp = cnt_prev + ((int64_t)g * cw.NB + min(lane, cw.nb_used - 1)) * K;
+    const int c = cp[0], ck = cp[min(wave, K - 1)];
+    // converged: the pass before changed nothing (NB <= 64 blocks, one lane each)
     if (!__ballot(c & kChangedBit)) {
       if (tid == 0) cnt_cur[slot * K] = 0;  // for the next pass, which reads this buffer
       return;
     }
+    // rows of cluster `wave` over all blocks
+    const int rows_k = wave_sum_int(lane < cw.nb_used ? (ck & 0xFFFF) : 0);
+    if (lane == 0 && wave < K) scnt[wave] = rows_k;
   } else if (!self && cw.conv[g]) {
     return;
   }
-  const int32_t* U = rest_list + (int64_t)g * n;
-  int32_t* asg = cw.assign + (int64_t)g * n;
-  for (int j = tid; j < nr; j += kClusterThreads) {
-    sidx[j] = U[j0 + j];
-    old[j] = pass > 0 ? asg[j0 + j] : -1;
+  if (tid < nr) {  // nr <= kMaxRowsPerBlock
+    sidx[tid] = u_j;
+    old[tid] = a_j;
   }
   if (tid == 0) chg = 0;
-  if (self && pass > 0 && wave < K) {
-    // rows of cluster `wave` over all blocks
-    const int c = wave_sum_int(lane < cw.nb_used ? (cnt_prev[((int64_t)g * cw.NB + lane) * K + wave] & 0xFFFF) : 0);
-    if (lane == 0) scnt[wave] = c;
-  }
   __syncthreads();
   const int row_bytes = d * (int)sizeof(FT);
   const int CH = chunk_rows(cw.RB, row_bytes);
@@ -800,28 +848,28 @@ __global__ void __launch_bounds__(kClusterThreads) cluster_sum_kernel(int n, int
       for (int e = 0; e < DP; ++e) acc[v][k][e] = 0.f;
   const int CH = chunk_rows(cw.RB, d * (int)sizeof(FT));
   const uint32_t lds = lds_offset(smem);
+  const int64_t slot = (int64_t)g * cw.NB + b;
   for (int c0 = 0; c0 < nr; c0 += CH) {
     const int cn = min(CH, nr - c0);
     if (c0 > 0) __syncthreads();
     stage_rows<FT>(fa, l, g, d, sidx + c0, cn, lds);
+    if (c0 == 0 && l == 0 && tid < K) {  // while the rows arrive
+      int c = 0;
+      float sm = 0.f;
+      for (int j = 0; j < nr; ++j) {
+        const bool mine = lab[j] == tid;
+        const float t = sm + sm_m[j];
+        c += mine;
+        sm = mine ? t : sm;
+      }
+      cw.pcnt[slot * K + tid] = c;
+      cw.pm[slot * K + tid] = sm;
+    }
     dma_wait_all();
     __syncthreads();
     add_rows<FT, KM, DP>(acc, smem, d, cn, lab + c0, sc + c0);
   }
-  const int64_t slot = (int64_t)g * cw.NB + b;
   store_sums<KM, DP>(acc, K, d, cw.psum + (slot * n_layers + l) * K * d);
-  if (l == 0 && tid >= kClusterThreads - 64 && tid - (kClusterThreads - 64) < K) {
-    const int k = tid - (kClusterThreads - 64);
-    int c = 0;
-    float sm = 0.f;
-    for (int j = 0; j < nr; ++j)
-      if (lab[j] == k) {
-        ++c;
-        sm += sm_m[j];
-      }
-    cw.pcnt[slot * K + k] = c;
-    cw.pm[slot * K + k] = sm;
-  }
 }
 
 // grid (ceil(L*K*d/256), G): mu = fixed-order sums / counts; mbar likewise.
@@ -1197,15 +1245,21 @@ extern "C" spider_status spider_score(int G, int n, int H, int d_v, int n_layers
   }
   {
     ProfScope ps(KC_ANCHOR_TOPK, st);
-    anchor_topk_kernel<<<G, 1024, 0, st>>>(n, n_anchor, a_out, cluster_out, s_out, ws.anc, ws.rest,
-                                            ws.cw.conv);
+    if (n <= 1024)
+      anchor_topk_kernel<16><<<G, 64, 0, st>>>(n, n_anchor, a_out, cluster_out, s_out, ws.anc, ws.rest, ws.cw.conv);
+    else
+      anchor_topk_kernel<kMaxN / 64><<<G, 64, 0, st>>>(n, n_anchor, a_out, cluster_out, s_out, ws.anc, ws.rest,
+                                                       ws.cw.conv);
     SPIDER_LAUNCHED("anchor_topk");
   }
   {
     ProfScope ps(KC_MAXSIM, st);
     const float* nu_last = ws.nu + (size_t)last * n;
     const int64_t nu_stride = (int64_t)n_layers * n;
-    if (feat_dtype == SPIDER_BF16)
+    if (feat_dtype == SPIDER_BF16 && ceil_div(n, 128) * G < kMaxsimBlocks)
+      anchor_maxsim_bf16_rows32_kernel<<<dim3(ceil_div(n, 32), G), 256, 0, st>>>(
+          n, d_v, n_anchor, fa, last, nu_last, nu_stride, ws.anc, ws.mvec);
+    else if (feat_dtype == SPIDER_BF16)
       anchor_maxsim_bf16_kernel<<<dim3(ceil_div(n, 128), G), 256, 0, st>>>(
           n, d_v, n_anchor, fa, last, nu_last, nu_stride, ws.anc, ws.mvec);
     else
