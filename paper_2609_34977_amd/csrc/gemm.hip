@@ -254,34 +254,41 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs a) {
 
 // ------------------------------------------------------------------ weight streaming
 // gemm_stream_kernel: up to 32*MT (<= 256) rows, the pruned-prefill regime.
-// 4 waves per block, one per SIMD, each owning 32 weight rows: non-dual, the
-// block covers 128 output columns; dual (SwiGLU), waves 0-1 take gate rows and
-// waves 2-3 up rows of the same 64 output columns, the up sums are handed over
-// through LDS and the epilogue writes bf16 silu(g) * u.
+// A block takes all rows against 32*NW weight rows: 32*NW output columns, or
+// (SwiGLU) 16*NW columns whose gate and up rows alternate in groups of 16, so
+// that one 32-row weight tile holds both.
 //
 // Both operands go global -> LDS with global_load_lds (no register round
-// trip) into a ring of LEAD+1 stages; a stage holds BM activation rows and the
-// block's 128 weight rows, 64 k each.  Every row is 128 B = eight 16-B chunks;
-// chunk c of row r sits in slot c ^ (r & 7), so the DMA writes (1 KB per
-// instruction, 8 rows of 8 lanes: a whole cache line per 8 lanes) and the MFMA
+// trip) into a ring of STAGES stages; a stage holds BM activation rows and the
+// block's weight rows, 64 k each.  Every row is 128 B = eight 16-B chunks;
+// chunk c of row r sits in slot c ^ swz(r), so the DMA writes (1 KB per
+// instruction, 8 rows of 8 lanes: a whole cache line per 8 lanes) and the MMA
 // fragment reads (32 rows, one chunk) are both free of bank conflicts.  Each
 // k-block is four v_mfma_f32_32x32x16_bf16 steps; step q takes chunk
 // 4*(lane/32) + q on both operands (a consistent permutation of k leaves every
 // dot product unchanged).
 //
+// 4 waves, one per SIMD: wave (wh, mh) takes row tiles [MH mh, MH mh + MH) and, for
+// even NW, half wh of the weight tiles.  Three weight tiles do not halve: there
+// wave (wh, mh) multiplies k-steps 2 wh and 2 wh + 1 of every k-block with all
+// three, and the two k halves are added through LDS at the end.  The weight
+// fragment is the MMA's A operand: a lane ends with one activation row and runs
+// of four consecutive weight rows.
+//
 // Pipeline: at iteration kb the block multiplies k-block kb, issues the DMA of
 // k-block kb+LEAD, waits until k-block kb+1 has landed and passes one barrier.
 // Every iteration issues the same loads (the tail re-reads the last k-block
 // into a slot never consumed), so the wait is an exact count of outstanding
-// loads; ring slots are compile-time (k-block kb lives in slot kb % (LEAD+1)).
-// Rows past M read row M-1 (their outputs are never stored).
+// loads; ring slots are compile-time (k-block kb lives in slot kb % STAGES).
+// Rows past M read row M-1, weight rows past N read row N-1 (never stored).
 //
-// Why this shape: at a few hundred rows the activation tile is 1.5x the
-// weight bytes of a block per k-block, and both streams compete for the
-// per-CU limit on outstanding L1 requests; whole-line weight requests (8
-// lanes per 128-B line) need a quarter of the L1 accesses of lane-per-row
-// register loads, and one block per column tile with the full row range reads
-// every weight once.
+// What bounds it: the two DMA streams, which add.  SwiGLU of a 4096 x 11008 pair
+// at 192 rows (230 blocks of 96 weight rows): 51 us; without the MMAs 50, the
+// weights alone 32 (HBM), the activations alone 20 (L2), the MMAs alone 33.
+// Deeper rings, rings and waves of their own for each operand, eight waves per
+// block and DMAs spread between the MMAs did not change that; what does is
+// every CU having a share of the weights (172 blocks of 128 rows took 61 us),
+// blocks out of step (below), and few split partials.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
@@ -308,32 +315,118 @@ __device__ __forceinline__ SoftStat soft_merge(SoftStat a, SoftStat b) {
 // bank groups (with c ^ (r & 7), rows r and r + 8 collide).
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
-template <int MT, int LEAD, bool DUAL, bool LENS = false>
+// Cache slot (in rows of d elements) of packed row `row`: its sample's first
+// slot plus its position.
+__device__ __forceinline__ int64_t cache_slot(const GemmArgs& a, int row) {
+  return (int64_t)(a.row_sample ? a.row_sample[row] : row) * a.kv_cap + a.pos[row];
+}
+
+// QKV epilogue of the streaming kernel: registers r and r + 8 (r < 8) of acc[i]
+// hold the rotate-half partners n0 + 16 wh + 8 (r / 4) + 4 hi + r % 4 and 64
+// columns on, of row tile i.  RoPE in place (kind bit 0), then bf16 through LDS:
+// [row][column] rows to `out` and to the cache slots of `out2`, or (kind 2) V^T
+// rows to `out`, whose rows M..ldvt-1 are written zero, and [row][column] rows to
+// the cache.  In LDS column n0 + c is c, its partner 32 + c.
+template <int MT, typename Acc, typename Trow>
+__device__ __forceinline__ void stream_qkv_epilogue(const GemmArgs& a, const GroupView& G, int kind, void* out2,
+                                                    uint8_t* ring, Acc& acc, int m0, int n0, int wh, int rows,
+                                                    Trow trow) {
+  constexpr int MH = MT / 2, BM = 32 * MT;
+  const int tid = threadIdx.x, hi = (tid & 63) >> 5;
+  const int c0 = 16 * wh + 4 * hi;  // local column of register 0
+  if (kind & 1) {
+#pragma unroll
+    for (int i = 0; i < MH; ++i) {
+      const int m = min(m0 + trow(i), G.M - 1);
+      const int p = a.pos[G.rows ? G.rows[m] : m];
+      const float4* cs = reinterpret_cast<const float4*>(a.rope + (int64_t)p * 64 + (n0 & 127) + c0);
+      float4 x[2][2];
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        x[g][0] = cs[4 * g];
+        x[g][1] = cs[4 * g + 1];
+      }
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const float c4[4] = {x[g][0].x, x[g][0].z, x[g][1].x, x[g][1].z};
+        const float s4[4] = {x[g][0].y, x[g][0].w, x[g][1].y, x[g][1].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float2 y = rope_rotate(acc[i][4 * g + e], acc[i][4 * g + e + 8], c4[e], s4[e]);
+          acc[i][4 * g + e] = y.x;
+          acc[i][4 * g + e + 8] = y.y;
+        }
+      }
+    }
+  }
+  uint16_t* st = reinterpret_cast<uint16_t*>(ring);
+  uint16_t* out = reinterpret_cast<uint16_t*>(G.out);
+  if (kind == 2 && out) {
+    constexpr int VP = BM + 8;
+    static_assert(64 * VP * 2 <= 64 * 1024, "V^T tile fits the ring");
+#pragma unroll
+    for (int i = 0; i < MH; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        st[(32 * (r >> 3) + c0 + 8 * ((r >> 2) & 1) + (r & 3)) * VP + trow(i)] =
+            f32_to_bf16_bits(trow(i) < rows ? acc[i][r] : 0.f);
+    __syncthreads();
+    for (int c = tid; c < 64 * (BM / 8); c += 256) {
+      const int col = c / (BM / 8), ch = c % (BM / 8);
+      if (m0 + 8 * ch < a.ldvt)
+        *reinterpret_cast<u32x4*>(out + (int64_t)(n0 + 64 * (col >> 5) + (col & 31)) * a.ldvt + m0 + 8 * ch) =
+            *reinterpret_cast<const u32x4*>(st + col * VP + 8 * ch);
+    }
+    if (!out2) return;
+    __syncthreads();
+  }
+  constexpr int QP = 72;  // row pitch (bf16)
+#pragma unroll
+  for (int i = 0; i < MH; ++i)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<uint2*>(st + trow(i) * QP + 32 * (g >> 1) + c0 + 8 * (g & 1)) =
+          make_uint2((uint32_t)f32_to_bf16_bits(acc[i][4 * g]) | ((uint32_t)f32_to_bf16_bits(acc[i][4 * g + 1]) << 16),
+                     (uint32_t)f32_to_bf16_bits(acc[i][4 * g + 2]) |
+                         ((uint32_t)f32_to_bf16_bits(acc[i][4 * g + 3]) << 16));
+  __syncthreads();
+  for (int c = tid; c < rows * 8; c += 256) {
+    const int row = c >> 3, ch = c & 7, m = m0 + row;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(st + row * QP + 8 * ch);
+    const int col = n0 + 64 * (ch >> 2) + 8 * (ch & 3);
+    if (kind != 2 && out) *reinterpret_cast<u32x4*>(out + (int64_t)m * G.ldo + col) = v;
+    if (out2)
+      *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out2) + cache_slot(a, G.rows ? G.rows[m] : m) * G.ldo +
+                                col) = v;
+  }
+}
+
+enum StreamMode { SM_PARTIAL, SM_SWIGLU, SM_LENS, SM_QKV };
+
+template <int NW, int MT, int MODE>
 __global__ void __launch_bounds__(256) gemm_stream_kernel(GemmArgs a) {
   constexpr int KB = 64;
-  // weights are read once: the SwiGLU and lens launches (split 1, whole K per
-  // block) load them non-temporal (measured 2-6 % faster there, no gain with split-K)
-  constexpr bool kWeightNT = DUAL || LENS;
-  constexpr int BM = 32 * MT;
-  constexpr int BN = DUAL ? 64 : 128;  // output columns per block
-  constexpr int STAGES = LEAD + 1;
+  constexpr bool DUAL = MODE == SM_SWIGLU;
+  // weights are read once: launches whose blocks take the whole K load them
+  // non-temporal (measured 2-6 % faster there, no gain with split-K)
+  constexpr bool kWeightNT = MODE != SM_PARTIAL;
+  constexpr int BM = 32 * MT, WR = 32 * NW, MH = MT / 2;
+  constexpr int BN = DUAL ? WR / 2 : WR;  // output columns per block
   constexpr int A_BYTES = BM * 128;
-  constexpr int STAGE_BYTES = A_BYTES + 128 * 128;  // activations, then the 128 weight rows
-  constexpr int PER_IT = 4 + MT;  // DMA instructions per wave per k-block: 4 weight, MT activation
-  // epilogue staging reuses the ring: dual hand-over + bf16 tile, or the fp32 tile (pitch 132)
-  constexpr int EPI_BYTES = DUAL ? 4 * (MT / 2) * 64 * 16 * 4 + BM * 72 * 2 : BM * 132 * 4;
-  constexpr int RING_BYTES = STAGES * STAGE_BYTES > EPI_BYTES ? STAGES * STAGE_BYTES : EPI_BYTES;
-  static_assert(RING_BYTES <= 160 * 1024, "LDS of one CU");
+  constexpr int STAGE_BYTES = A_BYTES + WR * 128;  // activations, then the weight rows
+  constexpr int STAGES = 4 * STAGE_BYTES <= 144 * 1024 ? 4 : 3, LEAD = STAGES - 1;
+  constexpr int PER_IT = NW + MT;  // DMA instructions per wave per k-block
+  constexpr int RING_BYTES = STAGES * STAGE_BYTES;
+  static_assert(MT % 2 == 0, "row tiles split over two waves");
+  static_assert(RING_BYTES <= 144 * 1024, "LDS of one block");
   __shared__ __attribute__((aligned(1024))) uint8_t ring[RING_BYTES];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hi = lane >> 5, lo = lane & 31;
-  constexpr int MH = MT / 2;
-  static_assert(MT % 2 == 0, "row tiles split over two waves");
-  const int mh = wave >> 1, nh = wave & 1;
-  // row of accumulator register r of row tile i, in the block (MMA D layout:
-  // column = lane % 32, row = 8 (r / 4) + 4 (lane / 32) + r % 4)
-  auto acc_row = [&](int i, int r) { return 32 * (MH * mh + i) + 8 * (r >> 2) + 4 * hi + (r & 3); };
+  const int mh = wave & 1, wh = wave >> 1;
+  constexpr bool KHALF = NW % 2 != 0;       // waves share the k-steps, not the weight tiles
+  constexpr int NWW = KHALF ? NW : NW / 2;  // weight tiles of a wave, from tile u0
+  const int u0 = KHALF ? 0 : NWW * wh;
   const TileCoord tc = decode_tile(a, xcd_remap(blockIdx.x, a.total_tiles), BM, BN);
   const GroupView G = group_view(a, tc.gi);
   const int M = G.M;
@@ -341,15 +434,21 @@ __global__ void __launch_bounds__(256) gemm_stream_kernel(GemmArgs a) {
   const int kbeg = tc.s * a.k_per_split;
   const int kend = min(a.K, kbeg + a.k_per_split);
   const int nkb = kend > kbeg ? (kend - kbeg) / KB : 0;
-  const int wrow0 = tc.n0 + 32 * (DUAL ? (wave & 1) : wave);  // first weight row of this wave
-  const uint16_t* W = reinterpret_cast<const uint16_t*>(DUAL && wave >= 2 ? G.W2 : G.W);
-  // weight DMA: instruction q fills the wave's rows 8q..8q+7; lane l takes row
-  // 8q + l/8, slot l%8
-  const uint16_t* pw[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)  // LDS weight row 32 wave + 8q + l/8
-    pw[q] = W + (int64_t)(wrow0 + 8 * q + (lane >> 3)) * a.K + kbeg + 8 * ((lane & 7) ^ swz(8 * q + (lane >> 3)));
+  // QKV: a block has 32 rotate-half pairs of one head, columns n0 + c and n0 + 64
+  // + c; a weight tile holds 16 columns and then their 16 partners
+  const int n0 = MODE == SM_QKV ? (tc.n0 & ~127) + (tc.n0 & 127) / 2 : tc.n0;
 
+  // weight DMA: instruction q fills LDS weight rows 8 (NW wave + q) .. + 7; lane
+  // l takes row l / 8 of them, slot l % 8
+  const uint16_t* pw[NW];
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    const int r = 8 * (NW * wave + q) + (lane >> 3), u = r >> 5, i = r & 31;
+    const uint16_t* W = reinterpret_cast<const uint16_t*>(DUAL && i >= 16 ? G.W2 : G.W);
+    const int row = DUAL ? n0 + 16 * u + (i & 15)
+                         : (MODE == SM_QKV ? n0 + 16 * u + (i & 15) + (i >= 16 ? 64 : 0) : n0 + r);
+    pw[q] = W + (int64_t)min(row, G.N - 1) * a.K + kbeg + 8 * ((lane & 7) ^ swz(r));
+  }
   // activation DMA: instruction j of this wave fills tile rows 8g..8g+7,
   // g = wave*MT + j; lane l takes row 8g + l/8, slot l%8
   const uint16_t* pa[MT];
@@ -362,64 +461,71 @@ __global__ void __launch_bounds__(256) gemm_stream_kernel(GemmArgs a) {
     pa[j] = reinterpret_cast<const uint16_t*>(G.A) + (int64_t)src * a.lda + kbeg + 8 * c;
   }
 
-  floatx16 acc[MT];
+  floatx16 acc[NWW][MH];
 #pragma unroll
-  for (int i = 0; i < MT; ++i) acc[i] = floatx16{};
+  for (int u = 0; u < NWW; ++u)
+#pragma unroll
+    for (int i = 0; i < MH; ++i) acc[u][i] = floatx16{};
 
   const uint32_t ring_lds = lds_offset(ring);
-  auto issue = [&](int kb, auto S) {
-    constexpr int st = decltype(S)::value;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      dma16<kWeightNT>(pw[q] + kb * KB, ring_lds + st * STAGE_BYTES + A_BYTES + (wave * 4 + q) * 1024);
-#pragma unroll
-    for (int j = 0; j < MT; ++j) dma16(pa[j] + kb * KB, ring_lds + st * STAGE_BYTES + (wave * MT + j) * 1024);
+  // Blocks with the whole K start at different k-blocks and wrap around: rows are
+  // a power-of-two stride apart, and blocks in step ask the same few L2 and
+  // memory channels (SwiGLU at 192 rows 55 -> 51 us, at 64 rows 39 -> 34; split
+  // launches lose by it: their blocks start apart already)
+  const int rot = a.split == 1 && nkb > 0 ? 5 * (tc.n0 / BN) % nkb : 0;
+  // DMA instruction p (of PER_IT per wave) of the kb-th k-block into stage S
+  auto issue_piece = [&](int kb, auto S, auto P) __attribute__((always_inline)) {
+    constexpr int st = decltype(S)::value, p = decltype(P)::value;
+    kb += rot;
+    kb -= kb >= nkb ? nkb : 0;
+    if constexpr (p < NW)
+      dma16<kWeightNT>(pw[p] + kb * KB, ring_lds + st * STAGE_BYTES + A_BYTES + (wave * NW + p) * 1024);
+    else
+      dma16(pa[p - NW] + kb * KB, ring_lds + st * STAGE_BYTES + (wave * MT + p - NW) * 1024);
   };
-  // Wave tile (2 x 2 over the block): rows [32 MH mh, 32 MH (mh + 1)) against LDS
-  // weight rows [64 nh, 64 nh + 64) -- output columns n0 + 64 nh.. (dual: nh 0
-  // the gate rows, 1 the up rows of the block's 64 columns).  Accumulator
-  // 2 i + t holds row tile i and column tile t.  Per k-step a wave reads MH + 2
-  // fragments from LDS for 2 MH MMAs.
-  auto compute = [&](auto S) {
+  // MMAs of the k-block in stage S, the DMA of k-block kbn into stage SN spread
+  // between them
+  auto compute = [&](auto S, int kbn, auto SN) __attribute__((always_inline)) {
     constexpr int st = decltype(S)::value;
-    const uint8_t* tile = ring + st * STAGE_BYTES;
-    const uint8_t* wt = tile + A_BYTES + (64 * nh + lo) * 128;
-    const uint8_t* at = tile + (32 * MH * mh + lo) * 128;
-    bf16x8 wf[2][2], af[2][MH];
-    auto frags = [&](int q, bf16x8 (&w)[2], bf16x8 (&x)[MH]) {
-      const int c = 16 * ((4 * hi + q) ^ swz(lo));
+    const uint8_t* wt = ring + st * STAGE_BYTES + A_BYTES + lo * 128;
+    const uint8_t* at = ring + st * STAGE_BYTES + (32 * MH * mh + lo) * 128;
+    constexpr int NQ = KHALF ? 2 : 4;
+    bf16x8 wf[2][NWW], af[2][MH];
+    auto frags = [&](int q, bf16x8 (&w)[NWW], bf16x8 (&x)[MH]) __attribute__((always_inline)) {
+      const int c = 16 * ((4 * hi + (KHALF ? 2 * wh : 0) + q) ^ swz(lo));
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-        w[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wt + t * 32 * 128 + c));
+      for (int u = 0; u < NWW; ++u)
+        w[u] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wt + (u0 + u) * 32 * 128 + c));
 #pragma unroll
       for (int i = 0; i < MH; ++i)
         x[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(at + i * 32 * 128 + c));
     };
     frags(0, wf[0], af[0]);
-    static_for<0, 4>([&](auto Q) {
+    static_for<0, NQ>([&](auto Q) {
       constexpr int q = Q.value;
-      if constexpr (q + 1 < 4) frags(q + 1, wf[(q + 1) & 1], af[(q + 1) & 1]);
+      if constexpr (q + 1 < NQ) frags(q + 1, wf[(q + 1) & 1], af[(q + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < MH; ++i)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-          acc[2 * i + t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[q & 1][i], wf[q & 1][t], acc[2 * i + t], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+      static_for<0, NWW * MH>([&](auto T) {
+        constexpr int t = T.value, i = t / NWW, u = t % NWW, n = q * NWW * MH + t, all = NQ * NWW * MH;
+        acc[u][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[q & 1][u], af[q & 1][i], acc[u][i], 0, 0, 0);
+        constexpr int p0 = n * PER_IT / all, p1 = (n + 1) * PER_IT / all;
+        static_for<p0, p1>([&](auto P) { issue_piece(kbn, SN, P); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
     });
   };
 
   if (nkb > 0) {
-    static_for<0, LEAD>([&](auto P) { issue(min((int)P.value, nkb - 1), P); });
+    static_for<0, LEAD>([&](auto S) {
+      static_for<0, PER_IT>([&](auto P) { issue_piece(min((int)S.value, nkb - 1), S, P); });
+    });
     dma_wait_barrier<(LEAD - 1) * PER_IT>();
     // k-block kb+LEAD goes to the slot that iteration kb-1 consumed (free since
-    // its barrier), before the MMAs of kb, so the loads overlap them; every
-    // iteration issues the same DMAs (the last k-block again at the end), so
-    // the count of DMAs still in flight is exact
+    // its barrier); every iteration issues the same DMAs (the last k-block again
+    // at the end), so the count of DMAs still in flight is exact
     auto body = [&](int kb, auto J) {
       constexpr int j = decltype(J)::value;
-      issue(min(kb + LEAD, nkb - 1), std::integral_constant<int, (j + LEAD) % STAGES>{});
-      compute(J);
+      compute(J, min(kb + LEAD, nkb - 1), std::integral_constant<int, (j + LEAD) % STAGES>{});
       dma_wait_barrier<(LEAD - 1) * PER_IT>();
     };
     int k0 = 0;
@@ -432,130 +538,163 @@ __global__ void __launch_bounds__(256) gemm_stream_kernel(GemmArgs a) {
     dma_wait_all();
   }
 
-  // D layout of 32x32 MFMA: n = lane % 32, m = 8*(r/4) + 4*(lane/32) + r%4
-  if constexpr (DUAL) {
-    // Waves (mh, 0) hold the gate sums of rows half mh, waves (mh, 1) the up sums
-    // of the same rows and columns.  Each pair splits the work by column tile:
-    // the gate wave finishes tile t = 0, the up wave t = 1, after trading the
-    // other tile through LDS.  The bf16 results are staged as a BM x 64
-    // row-major tile (pitch 72) and written with 16-byte stores, a whole
-    // 128-byte line per row.
-    constexpr int OPITCH = 72;
-    constexpr int XFER_BYTES = 4 * MH * 64 * 16 * 4;
-    static_assert(XFER_BYTES + BM * OPITCH * 2 <= RING_BYTES, "dual epilogue fits");
-    __syncthreads();  // ring free
-    float* xfer = reinterpret_cast<float*>(ring);
-    uint16_t* ot = reinterpret_cast<uint16_t*>(ring + XFER_BYTES);
-    // (dir, i): dir 0 carries up tile (i, 0) to the gate wave, dir 1 gate tile (i, 1) to the up wave
-    auto slot = [&](int dir, int i) { return xfer + (((mh * 2 + dir) * MH + i) * 64 + lane) * 16; };
-    auto put = [&](float* dst, const floatx16& v) {
+  // KHALF: add the two k halves.  The wh = 0 wave finishes the first OWN row
+  // tiles, the wh = 1 wave the rest, each handing the other's over through LDS.
+  // (The selects by wh are written out: a branch per half gets merged into one
+  // with a dynamic register index, which lives in scratch.)
+  constexpr int OWN = KHALF ? (MH + 1) / 2 : MH;
+  static_assert(!KHALF || NW * MT * 4096 <= RING_BYTES, "hand-over fits the ring");
+  __syncthreads();  // ring free
+  floatx16 fin[NWW][OWN];
+  if constexpr (KHALF) {
+    auto pick = [&](int u, int j0, int j1) {  // wh ? acc[u][j1] : acc[u][j0]
+      floatx16 v;
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<floatx4*>(dst + 4 * q) = floatx4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+      for (int e = 0; e < 16; ++e) v[e] = wh ? acc[u][j1][e] : acc[u][j0][e];
+      return v;
     };
-    if (nh == 0) {
+    float* hand = reinterpret_cast<float*>(ring) + mh * MH * NW * 1024 + lane * 4;
 #pragma unroll
-      for (int i = 0; i < MH; ++i) put(slot(1, i), acc[2 * i + 1]);
-    } else {
+    for (int j = 0; j < OWN; ++j)
 #pragma unroll
-      for (int i = 0; i < MH; ++i) put(slot(0, i), acc[2 * i]);
-    }
-    __syncthreads();
-    if (nh == 0) {
+      for (int u = 0; u < NW; ++u) {
+        const floatx16 v = pick(u, OWN + j < MH ? OWN + j : j, j);
+        if (wh || OWN + j < MH) {
 #pragma unroll
-      for (int i = 0; i < MH; ++i) {
-        const float* up = slot(0, i);
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          ot[acc_row(i, r) * OPITCH + lo] = f32_to_bf16_bits(silu(acc[2 * i][r]) * up[r]);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < MH; ++i) {
-        const float* gp = slot(1, i);
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          ot[acc_row(i, r) * OPITCH + 32 + lo] = f32_to_bf16_bits(silu(gp[r]) * acc[2 * i + 1][r]);
-      }
-    }
-    __syncthreads();
-    const int rows = min(BM, M - tc.m0);
-    uint16_t* op = reinterpret_cast<uint16_t*>(G.out) + (int64_t)tc.m0 * G.ldo + tc.n0;
-    for (int c = tid; c < rows * 8; c += 256) {
-      const int row = c >> 3, ch = c & 7;
-      *reinterpret_cast<u32x4*>(op + (int64_t)row * G.ldo + 8 * ch) =
-          *reinterpret_cast<const u32x4*>(ot + row * OPITCH + 8 * ch);
-    }
-  } else if constexpr (LENS) {
-    // the block's BM x 128 logits go through LDS (row pitch 132 floats); each
-    // row is reduced by 256/BM threads (64 rows: 4, 128: 2, 192/256: 1) over
-    // consecutive column ranges, merged across those threads in fixed order
-    constexpr int PITCH = 132;
-    constexpr int TPR = BM <= 64 ? 4 : (BM <= 128 ? 2 : 1);
-    constexpr int CPT = 128 / TPR;
-    static_assert(BM * PITCH * 4 <= RING_BYTES, "lens tile fits the ring");
-    __syncthreads();
-    float* sm = reinterpret_cast<float*>(ring);
-#pragma unroll
-    for (int i = 0; i < MH; ++i)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sm[acc_row(i, r) * PITCH + 64 * nh + 32 * t + lo] = acc[2 * i + t][r];
-    __syncthreads();
-    const int row = tid / TPR, part = tid % TPR;
-    SoftStat st{-INFINITY, 0.f, 0.f};
-    if (row < BM) {
-      const float* z = sm + row * PITCH + part * CPT;
-      float mx = -INFINITY;
-#pragma unroll
-      for (int c = 0; c < CPT; c += 4) {
-        const floatx4 v = *reinterpret_cast<const floatx4*>(z + c);
-        mx = fmaxf(mx, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
-      }
-      float se = 0.f, te = 0.f;
-#pragma unroll
-      for (int c = 0; c < CPT; c += 4) {
-        const floatx4 v = *reinterpret_cast<const floatx4*>(z + c);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float u = v[e] - mx;
-          const float x = expf(u);
-          se += x;
-          te = fmaf(x, u, te);
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<floatx4*>(hand + (((wh ? j : OWN + j) * NW + u) * 4 + q) * 256) =
+                floatx4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
         }
       }
-      st = {mx, se, te};
-    }
-#pragma unroll
-    for (int o = 1; o < TPR; o <<= 1) {
-      const SoftStat other{__shfl_xor(st.m, o, 64), __shfl_xor(st.s, o, 64), __shfl_xor(st.t, o, 64)};
-      st = (part & o) ? soft_merge(other, st) : soft_merge(st, other);
-    }
-    const int m = tc.m0 + row;
-    if (row < BM && part == 0 && m < M)
-      *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(G.out) +
-                                  ((int64_t)m * G.ldo + tc.n0 / 128) * 4) = floatx4{st.m, st.s, st.t, 0.f};
-  } else {
-    // fp32 partial sums go through LDS (row pitch 132 floats) so that every
-    // thread stores 16-byte pieces: 32 threads cover a 512-byte row segment
-    constexpr int PITCH = 132;
-    static_assert(BM * PITCH * 4 <= RING_BYTES, "partial tile fits the ring");
     __syncthreads();
+#pragma unroll
+    for (int j = 0; j < OWN; ++j)
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        fin[u][j] = pick(u, j, OWN + j < MH ? OWN + j : j);
+        if (!wh || OWN + j < MH) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const floatx4 v = *reinterpret_cast<const floatx4*>(hand + (((wh ? OWN + j : j) * NW + u) * 4 + q) * 256);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) fin[u][j][4 * q + e] += v[e];
+          }
+        }
+      }
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int u = 0; u < NWW; ++u)
+#pragma unroll
+      for (int j = 0; j < OWN; ++j) fin[u][j] = acc[u][j];
+  }
+  auto mine = [&](int j) { return !KHALF || !wh || OWN + j < MH; };
+
+  // D layout: weight row 8 g + 4 hi + e of tile u in register 4 g + e, activation
+  // row lo of the wave's row tile i.  Results go through LDS so that the stores are whole
+  // row pieces.
+  const int rows = min(BM, M - tc.m0);
+  auto trow = [&](int j) { return 32 * (MH * mh + (KHALF && wh ? OWN : 0) + j) + lo; };
+  if constexpr (DUAL) {
+    // weight rows 0..15 of a tile are gate rows, 16..31 the up rows of the same
+    // columns: registers r and r + 8 of one lane
+    constexpr int OPITCH = BN + 8;
+    static_assert(BM * OPITCH * 2 <= RING_BYTES, "output tile fits the ring");
+    uint16_t* ot = reinterpret_cast<uint16_t*>(ring);
+#pragma unroll
+    for (int i = 0; i < OWN; ++i)
+      if (mine(i)) {
+#pragma unroll
+        for (int u = 0; u < NWW; ++u)
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            uint32_t w[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const int r = 4 * g + 2 * e;
+              w[e] = (uint32_t)f32_to_bf16_bits(silu(fin[u][i][r]) * fin[u][i][r + 8]) |
+                     ((uint32_t)f32_to_bf16_bits(silu(fin[u][i][r + 1]) * fin[u][i][r + 9]) << 16);
+            }
+            *reinterpret_cast<uint2*>(ot + trow(i) * OPITCH + 16 * (u0 + u) + 8 * g + 4 * hi) = make_uint2(w[0], w[1]);
+          }
+      }
+    __syncthreads();
+    uint16_t* op = reinterpret_cast<uint16_t*>(G.out) + (int64_t)tc.m0 * G.ldo + n0;
+    constexpr int PIECES = BN / 8;
+    for (int c = tid; c < rows * PIECES; c += 256) {
+      const int row = c / PIECES, ch = c % PIECES;
+      if (n0 + 8 * ch < G.N)
+        *reinterpret_cast<u32x4*>(op + (int64_t)row * G.ldo + 8 * ch) =
+            *reinterpret_cast<const u32x4*>(ot + row * OPITCH + 8 * ch);
+    }
+  } else if constexpr (MODE == SM_QKV) {
+    static_assert(NW == 2, "a weight tile per wave half");
+    stream_qkv_epilogue<MT>(a, G, sel3(tc.gi, a.g[0].kind, a.g[1].kind, a.g[2].kind),
+                            sel3(tc.gi, a.g[0].out2, a.g[1].out2, a.g[2].out2), ring, fin[0], tc.m0, n0, wh, rows, trow);
+  } else {
+    // fp32 tile, row pitch WR + 4 floats
+    constexpr int PITCH = WR + 4;
+    static_assert(BM * PITCH * 4 <= RING_BYTES, "fp32 tile fits the ring");
     float* sm = reinterpret_cast<float*>(ring);
 #pragma unroll
-    for (int i = 0; i < MH; ++i)
+    for (int i = 0; i < OWN; ++i)
+      if (mine(i)) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+        for (int u = 0; u < NWW; ++u)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sm[acc_row(i, r) * PITCH + 64 * nh + 32 * t + lo] = acc[2 * i + t][r];
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<floatx4*>(sm + trow(i) * PITCH + 32 * (u0 + u) + 8 * g + 4 * hi) =
+                floatx4{fin[u][i][4 * g], fin[u][i][4 * g + 1], fin[u][i][4 * g + 2], fin[u][i][4 * g + 3]};
+      }
     __syncthreads();
-    const int rows = min(BM, M - tc.m0);
-    float* op = reinterpret_cast<float*>(G.out) + tc.s * G.sstride + (int64_t)tc.m0 * G.ldo + tc.n0;
-    for (int c = tid; c < rows * 32; c += 256) {
-      const int row = c >> 5, ch = c & 31;
-      *reinterpret_cast<floatx4*>(op + (int64_t)row * G.ldo + 4 * ch) =
-          *reinterpret_cast<const floatx4*>(sm + row * PITCH + 4 * ch);
+    if constexpr (MODE == SM_LENS) {
+      // each row's 128 logits are reduced by 256/BM threads (64 rows: 4, 128: 2,
+      // 192/256: 1) over consecutive column ranges, merged in fixed order
+      constexpr int TPR = BM <= 64 ? 4 : (BM <= 128 ? 2 : 1);
+      constexpr int CPT = 128 / TPR;
+      const int row = tid / TPR, part = tid % TPR;
+      SoftStat st{-INFINITY, 0.f, 0.f};
+      if (row < BM) {
+        const float* z = sm + row * PITCH + part * CPT;
+        float mx = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < CPT; c += 4) {
+          const floatx4 v = *reinterpret_cast<const floatx4*>(z + c);
+          mx = fmaxf(mx, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+        }
+        float se = 0.f, te = 0.f;
+#pragma unroll
+        for (int c = 0; c < CPT; c += 4) {
+          const floatx4 v = *reinterpret_cast<const floatx4*>(z + c);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float u = v[e] - mx;
+            const float x = expf(u);
+            se += x;
+            te = fmaf(x, u, te);
+          }
+        }
+        st = {mx, se, te};
+      }
+#pragma unroll
+      for (int o = 1; o < TPR; o <<= 1) {
+        const SoftStat other{__shfl_xor(st.m, o, 64), __shfl_xor(st.s, o, 64), __shfl_xor(st.t, o, 64)};
+        st = (part & o) ? soft_merge(other, st) : soft_merge(st, other);
+      }
+      const int m = tc.m0 + row;
+      if (row < BM && part == 0 && m < M)
+        *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(G.out) + ((int64_t)m * G.ldo + n0 / 128) * 4) =
+            floatx4{st.m, st.s, st.t, 0.f};
+    } else {
+      // fp32 partial sums as 16-byte pieces
+      float* op = reinterpret_cast<float*>(G.out) + tc.s * G.sstride + (int64_t)tc.m0 * G.ldo + n0;
+      constexpr int PIECES = WR / 4;
+      for (int c = tid; c < rows * PIECES; c += 256) {
+        const int row = c / PIECES, ch = c % PIECES;
+        if (n0 + 4 * ch < G.N)
+          *reinterpret_cast<floatx4*>(op + (int64_t)row * G.ldo + 4 * ch) =
+              *reinterpret_cast<const floatx4*>(sm + row * PITCH + 4 * ch);
+      }
     }
   }
 }
@@ -900,40 +1039,51 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(GemmArgs a) {
     uint16_t* sw = reinterpret_cast<uint16_t*>(ring) + wave * WAREA;
     const int col0 = n0 + 128 * nh;
     uint16_t* out = reinterpret_cast<uint16_t*>(G.out);
+    uint16_t* out2 = reinterpret_cast<uint16_t*>(sel3(gi, a.g[0].out2, a.g[1].out2, a.g[2].out2));
+    auto put_rows = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<uint2*>(sw + lo * QP + 32 * u + 8 * g + 4 * hi) =
+              make_uint2((uint32_t)f32_to_bf16_bits(acc[i][u][4 * g]) |
+                             ((uint32_t)f32_to_bf16_bits(acc[i][u][4 * g + 1]) << 16),
+                         (uint32_t)f32_to_bf16_bits(acc[i][u][4 * g + 2]) |
+                             ((uint32_t)f32_to_bf16_bits(acc[i][u][4 * g + 3]) << 16));
+    };
+    // [row][column] rows of the tile at rb: to out (Q, K) and to the cache
+    auto store_rows = [&](int rb) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int row = (lane >> 4) + 4 * j, ch = lane & 15;
+        if (rb + row >= M) continue;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(sw + row * QP + 8 * ch);
+        if (kind == 1 && out) *reinterpret_cast<u32x4*>(out + (int64_t)(rb + row) * G.ldo + col0 + 8 * ch) = v;
+        if (out2)
+          *reinterpret_cast<u32x4*>(out2 + cache_slot(a, G.rows ? G.rows[rb + row] : rb + row) * G.ldo + col0 + 8 * ch) = v;
+      }
+    };
 #pragma unroll
     for (int i = 0; i < MH; ++i) {
       const int rb = m0 + 32 * (MH * mh + i);  // first row of the tile
       __syncthreads();
       if (i < live) {
+        if (kind == 1) {
+          put_rows(i);
+        } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+          for (int u = 0; u < 4; ++u)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int col = 32 * u + 8 * g + 4 * hi;
-            if (kind == 1) {
-              *reinterpret_cast<uint2*>(sw + lo * QP + col) =
-                  make_uint2((uint32_t)f32_to_bf16_bits(acc[i][u][4 * g]) |
-                                 ((uint32_t)f32_to_bf16_bits(acc[i][u][4 * g + 1]) << 16),
-                             (uint32_t)f32_to_bf16_bits(acc[i][u][4 * g + 2]) |
-                                 ((uint32_t)f32_to_bf16_bits(acc[i][u][4 * g + 3]) << 16));
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                sw[(col + e) * VP + lo] = f32_to_bf16_bits(rb + lo < M ? acc[i][u][4 * g + e] : 0.f);
-            }
-          }
+            for (int r = 0; r < 16; ++r)
+              sw[(32 * u + 8 * (r >> 2) + 4 * hi + (r & 3)) * VP + lo] =
+                  f32_to_bf16_bits(rb + lo < M ? acc[i][u][r] : 0.f);
+        }
       }
       __syncthreads();
       if (i < live) {
         if (kind == 1) {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int row = (lane >> 4) + 4 * j, ch = lane & 15;
-            if (rb + row < M)
-              *reinterpret_cast<u32x4*>(out + (int64_t)(rb + row) * G.ldo + col0 + 8 * ch) =
-                  *reinterpret_cast<const u32x4*>(sw + row * QP + 8 * ch);
-          }
-        } else {
+          store_rows(rb);
+        } else if (out) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const int c = (lane >> 2) + 16 * j, ch = lane & 3;
@@ -942,6 +1092,12 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(GemmArgs a) {
                   *reinterpret_cast<const u32x4*>(sw + c * VP + 8 * ch);
           }
         }
+      }
+      if (kind == 2 && out2) {  // the values again, as rows for the cache
+        __syncthreads();
+        if (i < live) put_rows(i);
+        __syncthreads();
+        if (i < live) store_rows(rb);
       }
     }
   } else {
@@ -1188,30 +1344,15 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs a) {
   }
 }
 
-struct TileCfg {
-  int BM, BN;
-  bool stream;  // weight-streaming kernel
-};
-
-// Tile shape.  Up to 256 rows the weight-streaming kernel covers every row in
-// one tile (BM = rows rounded up to 64), so each weight element is read from
-// HBM once; more rows use the LDS-staged kernel.
-TileCfg pick_bf16_tile(int maxM, bool dual) {
-  if (maxM <= 256) {
-    const int bm = std::max(64, (maxM + 63) / 64 * 64);
-    return TileCfg{bm, dual ? 64 : 128, true};
-  }
-  return dual ? TileCfg{128, 64, false} : TileCfg{128, 128, false};
-}
-
 constexpr int kTargetBlocks = 256;
 
-// LDS-staged kernel: split until the grid covers the chip.  Streaming kernel
-// (one block per CU): the largest split whose grid still fits in one wave of
-// blocks; a second partial wave costs more than it hides.
-int choose_split(int tiles, int K, int split_max, int kgran, bool stream) {
+// Split-K of the tile and LDS-staged kernels.  Tile kernel (one block per CU):
+// the largest split whose grid still fits in one wave of blocks; a second
+// partial wave costs more than it hides.  LDS-staged kernel: split until the
+// grid covers the chip.
+int choose_split(int tiles, int K, int split_max, int kgran, bool one_wave) {
   int split = 1;
-  if (stream) {
+  if (one_wave) {
     while (split < split_max && tiles * split * 2 <= kTargetBlocks && K / (kgran * split * 2) >= 4) split *= 2;
   } else {
     while (split < split_max && tiles * split < kTargetBlocks && K / (kgran * split * 2) >= 4) split *= 2;
@@ -1219,12 +1360,54 @@ int choose_split(int tiles, int K, int split_max, int kgran, bool stream) {
   return split;
 }
 
+// Weight tiles per block and split of a streaming launch: the least of
+//   waves of blocks x (k-blocks of a block x (NW + kStreamAct) + kStreamFixed)
+//   + split x output columns x kStreamPartial
+// in units of one 32-row weight tile's k-block (0.14 us on a CU): the 192
+// activation rows of a k-block cost about 1.7 weight tiles, a block's prologue
+// and epilogue about 20, and the partial sums are written here and read again by
+// the next kernel.  At 192 rows it takes, per launch, NW 3 for SwiGLU (51 us; 4:
+// 61), NW 2 and split 4 for O (16.2 us; 4 and 8: 17.3 and a norm 1 us longer), NW
+// 4 and split 8 for down (30 us; 2 and 4: 36).  It depends on the columns and K
+// only, never on the row count: launches sized for a row bound give the bits of
+// launches sized for the live rows.
+constexpr double kStreamAct = 1.7, kStreamFixed = 20.0, kStreamPartial = 5.2 / 4096;
+
+struct StreamChoice {
+  int nw, split;
+};
+
+StreamChoice stream_choice(const GemmArgs& a, int split_max, bool dual) {
+  StreamChoice best{4, 1};
+  double best_cost = 1e300;
+  const int nkb = a.K / 64;
+  for (int nw : {4, 3, 2}) {
+    if (nw == 3 && !dual) continue;  // the hand-over of the k halves costs a short block more than it saves
+    const int bn = dual ? 16 * nw : 32 * nw;
+    int tiles = 0;
+    double cols = 0;
+    for (int i = 0; i < a.ngroups; ++i) {
+      tiles += ceil_div(a.g[i].N, bn);
+      cols += a.g[i].N;
+    }
+    for (int split = 1; split <= (dual ? 1 : split_max) && (split == 1 || nkb / split >= 4); ++split) {
+      const double cost = ceil_div(tiles * split, kTargetBlocks) * (ceil_div(nkb, split) * (nw + kStreamAct) + kStreamFixed) +
+                          (dual ? 0.0 : split * cols * kStreamPartial);
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = StreamChoice{nw, split};
+      }
+    }
+  }
+  return best;
+}
+
 void fill_tiles(GemmArgs& a, int BM, int BN) {
   int t = 0;
   for (int i = 0; i < a.ngroups; ++i) {
     GemmGroup& g = a.g[i];
     g.tiles_m = ceil_div(g.M, BM);
-    g.tiles_n = g.N / BN;
+    g.tiles_n = ceil_div(g.N, BN);  // only the streaming kernel takes a ragged last tile
     g.tile_begin = t;
     t += g.tiles_m * g.tiles_n * a.split;
   }
@@ -1242,10 +1425,26 @@ void launch_cfg(const GemmArgs& a, hipStream_t st) {
   gemm_bf16_kernel<BM, BN, WGM, WGN, 4, DUAL><<<a.total_tiles, 256, 0, st>>>(a);
 }
 
-template <int MT, bool DUAL, bool LENS = false>
-void launch_stream(const GemmArgs& a, hipStream_t st) {
-  constexpr int LEAD = MT <= 2 ? 3 : 2;
-  gemm_stream_kernel<MT, LEAD, DUAL, LENS><<<a.total_tiles, 256, 0, st>>>(a);
+template <int NW, int MODE>
+void launch_stream(const GemmArgs& a, int maxM, hipStream_t st) {
+  switch (std::max(1, ceil_div(maxM, 64))) {
+    case 1: gemm_stream_kernel<NW, 2, MODE><<<a.total_tiles, 256, 0, st>>>(a); break;
+    case 2: gemm_stream_kernel<NW, 4, MODE><<<a.total_tiles, 256, 0, st>>>(a); break;
+    case 3: gemm_stream_kernel<NW, 6, MODE><<<a.total_tiles, 256, 0, st>>>(a); break;
+    default: gemm_stream_kernel<NW, 8, MODE><<<a.total_tiles, 256, 0, st>>>(a); break;
+  }
+}
+
+// The streaming kernel stores 16-byte pieces of output rows and multiplies whole
+// 64-k blocks.
+bool stream_fits(const GemmArgs& a, int maxM, bool dual) {
+  if (maxM > 256 || a.K % 64) return false;
+  const int per16 = dual ? 8 : 4;
+  for (int i = 0; i < a.ngroups; ++i) {
+    const GemmGroup& g = a.g[i];
+    if (g.N % 16 || reinterpret_cast<uintptr_t>(g.out) % 16 || g.ldo % per16 || g.split_stride % per16) return false;
+  }
+  return true;
 }
 
 // More than 256 rows: gemm_tile_kernel when the shapes fit it (N a multiple of
@@ -1401,17 +1600,13 @@ bool has_row_count(const GemmArgs& a) {
 }
 }  // namespace
 
-int gemm_tile_unsplit_blocks(const GemmArgs& a, int split_max) {
+bool gemm_qkv_fused(const GemmArgs& a, int split_max) {
   const int maxM = max_rows(a);
-  if (gemv_fits(maxM, a.K) || maxM <= 256 || !tile_path_fits(a, false)) return 0;
-  const TileChoice tc = tile_choice(a, split_max, false);
-  return tc.split == 1 ? tiles_for(a, 64 * tc.mh, 256) : 0;
-}
-
-int gemm_split_for(int M, int N, int K, bool dual, bool bf16, int split_max) {
-  if (dual || !bf16) return 1;
-  TileCfg tc = pick_bf16_tile(M, false);
-  return choose_split(ceil_div(M, tc.BM) * (N / tc.BN), K, split_max, tc.stream ? 64 : 32, tc.stream);
+  if (gemv_fits(maxM, a.K) || a.K % 64) return false;
+  for (int i = 0; i < a.ngroups; ++i)
+    if (a.g[i].N % 128) return false;
+  if (maxM <= 256) return true;
+  return !has_row_count(a) && tile_path_fits(a, false) && tile_choice(a, split_max, false).split == 1;
 }
 
 hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
@@ -1422,29 +1617,30 @@ hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
       if (a.g[i].N % 128) return hipErrorInvalidValue;
     a.split = 1;
     a.k_per_split = a.K;
-    const int bm = std::max(64, (maxM + 63) / 64 * 64);
-    fill_tiles(a, bm, 128);
+    fill_tiles(a, 256, 128);
     if (a.total_tiles == 0) return hipSuccess;
-    switch (bm) {
-      case 64: launch_stream<2, false, true>(a, st); break;
-      case 128: launch_stream<4, false, true>(a, st); break;
-      case 192: launch_stream<6, false, true>(a, st); break;
-      default: launch_stream<8, false, true>(a, st); break;
-    }
+    launch_stream<4, SM_LENS>(a, maxM, st);
     return hipGetLastError();
   }
   const bool dual = a.epilogue == EPI_SWIGLU;
   const bool gemv_ok = gemv_fits(maxM, a.K);
-  if (a.epilogue == EPI_QKV_BF16 && has_row_count(a)) return hipErrorInvalidValue;
   if (a.epilogue == EPI_QKV_BF16) {
-    // the tile kernel without split, one head of 128 columns per wave, 16-byte stores
-    if (gemm_tile_unsplit_blocks(a, split_max) == 0 || !a.rope || !a.pos) return hipErrorInvalidValue;
+    // whole sums in one block, whole heads, 16-byte stores
+    if (!gemm_qkv_fused(a, split_max) || !a.rope || !a.pos) return hipErrorInvalidValue;
     for (int i = 0; i < a.ngroups; ++i) {
       const GemmGroup& g = a.g[i];
-      if (reinterpret_cast<uintptr_t>(g.out) % 16) return hipErrorInvalidValue;
-      if (g.kind == 1 ? g.ldo % 8 != 0 : (g.kind != 2 || a.ldvt % 32 || a.ldvt < g.M)) return hipErrorInvalidValue;
+      if (reinterpret_cast<uintptr_t>(g.out) % 16 || reinterpret_cast<uintptr_t>(g.out2) % 16 || g.ldo % 8 ||
+          (g.kind != 1 && g.kind != 2) || (g.out2 && a.kv_cap < 1))
+        return hipErrorInvalidValue;
+      if (g.kind == 2 && g.out && (a.ldvt % 32 || a.ldvt < g.M)) return hipErrorInvalidValue;
     }
-    return launch_tile(a, split_max, false, st);
+    if (maxM > 256) return launch_tile(a, split_max, false, st);
+    a.split = 1;
+    a.k_per_split = a.K;
+    fill_tiles(a, 256, 64);
+    if (a.total_tiles == 0) return hipSuccess;
+    launch_stream<2, SM_QKV>(a, maxM, st);
+    return hipGetLastError();
   }
   if (a.epilogue == EPI_RESIDUAL_F32 || a.epilogue == EPI_DECODE_QKV || a.norm_h) {
     // only the decode-row kernel applies a residual or cache epilogue or a
@@ -1459,41 +1655,38 @@ hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
   if ((gemv_ok || (maxM > 256 && tile_path_fits(a, dual))) && has_row_count(a)) return hipErrorInvalidValue;
   if (gemv_ok) return launch_gemv(a, maxM, dual, st);
   if (maxM > 256 && tile_path_fits(a, dual)) return launch_tile(a, split_max, dual, st);
-  TileCfg tc = pick_bf16_tile(maxM, dual);
-  // the streaming kernel's epilogue stores 16-byte pieces of output rows
-  auto vec_out = [&](const GemmGroup& g) {
-    const int per16 = dual ? 8 : 4;
-    return reinterpret_cast<uintptr_t>(g.out) % 16 == 0 && g.ldo % per16 == 0 && g.split_stride % per16 == 0;
-  };
-  // Shapes the streaming and tile kernels do not take go to the LDS-staged kernel
-  // (up to 256 rows a tile of all rows, non-dual; the SwiGLU launch fits the
-  // streaming kernel whenever K and N are multiples of 64 and its output is
-  // aligned, so its fallback is the 128 x 64 tile at any row count)
-  for (int i = 0; i < a.ngroups; ++i)
-    if (a.g[i].N % tc.BN || (tc.stream && (a.K % 64 || !vec_out(a.g[i])))) {
-      tc = maxM <= 256 && !dual ? TileCfg{std::max(64, (maxM + 63) / 64 * 64), 64, false}
-                                : TileCfg{128, dual ? 64 : 128, false};
-      break;
+  if (stream_fits(a, maxM, dual)) {
+    const StreamChoice sc = stream_choice(a, split_max, dual);
+    a.split = sc.split;
+    a.k_per_split = ceil_div(a.K / 64, a.split) * 64;
+    fill_tiles(a, 256, (dual ? 16 : 32) * sc.nw);
+    if (a.total_tiles == 0) return hipSuccess;
+    switch (sc.nw * 2 + (dual ? 1 : 0)) {
+      case 4: launch_stream<2, SM_PARTIAL>(a, maxM, st); break;
+      case 5: launch_stream<2, SM_SWIGLU>(a, maxM, st); break;
+      case 7: launch_stream<3, SM_SWIGLU>(a, maxM, st); break;
+      case 8: launch_stream<4, SM_PARTIAL>(a, maxM, st); break;
+      default: launch_stream<4, SM_SWIGLU>(a, maxM, st); break;
     }
+    return hipGetLastError();
+  }
+  // Shapes the streaming and tile kernels do not take go to the LDS-staged
+  // kernel: non-dual up to 256 rows a tile of all rows, otherwise 128-row tiles
+  // (the SwiGLU launch up to 256 rows always fits the streaming kernel: K and N
+  // are multiples of 64 and its output is aligned)
+  const int BM = maxM <= 256 && !dual ? std::max(64, (maxM + 63) / 64 * 64) : 128;
+  const int BN = dual || maxM <= 256 ? 64 : 128;
   for (int i = 0; i < a.ngroups; ++i)
-    if (a.g[i].N % tc.BN) return hipErrorInvalidValue;
-  const int kgran = tc.stream ? 64 : 32;
-  if (a.K % kgran) return hipErrorInvalidValue;
-  a.split = dual ? 1 : choose_split(tiles_for(a, tc.BM, tc.BN), a.K, split_max, kgran, tc.stream);
-  a.k_per_split = ceil_div(ceil_div(a.K, kgran), a.split) * kgran;
-  fill_tiles(a, tc.BM, tc.BN);
+    if (a.g[i].N % BN) return hipErrorInvalidValue;
+  if (a.K % 32) return hipErrorInvalidValue;
+  a.split = dual ? 1 : choose_split(tiles_for(a, BM, BN), a.K, split_max, 32, false);
+  a.k_per_split = ceil_div(a.K / 32, a.split) * 32;
+  fill_tiles(a, BM, BN);
   if (a.total_tiles == 0) return hipSuccess;
-  if (tc.stream) {
-    switch (tc.BM) {
-      case 64: dual ? launch_stream<2, true>(a, st) : launch_stream<2, false>(a, st); break;
-      case 128: dual ? launch_stream<4, true>(a, st) : launch_stream<4, false>(a, st); break;
-      case 192: dual ? launch_stream<6, true>(a, st) : launch_stream<6, false>(a, st); break;
-      default: dual ? launch_stream<8, true>(a, st) : launch_stream<8, false>(a, st); break;
-    }
-  } else if (dual) {
+  if (dual) {
     launch_cfg<128, 64, 2, 2, true>(a, st);
   } else {
-    switch (tc.BM * 1000 + tc.BN) {
+    switch (BM * 1000 + BN) {
       case 64064: launch_cfg<64, 64, 2, 2, false>(a, st); break;
       case 128064: launch_cfg<128, 64, 2, 2, false>(a, st); break;
       case 192064: launch_cfg<192, 64, 2, 2, false>(a, st); break;

@@ -18,11 +18,15 @@ struct GemmGroup {
   int64_t split_stride;   // elements between split-K slabs of out
   int tiles_m, tiles_n;   // filled by the launcher
   int tile_begin;         // filled by the launcher
-  int kind;               // EPI_QKV_BF16 only: 1 = RoPE'd rows (Q, K), 2 = transposed rows (V^T)
+  int kind;               // EPI_QKV_BF16: 1 = RoPE'd rows (Q, K), 2 = transposed rows (V^T)
   // Optional device row count: the kernel takes min(M, *m_dev) rows (M is then
   // the bound the launch is sized for).  Streaming, LDS-staged and fp32
   // kernels only; the launcher rejects it where it would pick another kernel.
   const int32_t* m_dev;
+  // EPI_QKV_BF16: optional KV cache rows; row m also goes, untransposed, to
+  // out2 + slot * ldo, slot = its sample * kv_cap + its position (out may then
+  // be null: cache only)
+  void* out2;
 };
 
 enum GemmEpilogue {
@@ -33,8 +37,8 @@ enum GemmEpilogue {
                         // M <= 256, N % 128 == 0, K % 64 == 0, no split
   EPI_RESIDUAL_F32 = 3,  // out fp32 [M][N] += A W^T; bf16, M <= 4 only (decode), no split
   EPI_QKV_BF16 = 4,      // bf16 out per group kind: 1 = rotate-half RoPE at pos[row] (row = a_rows[m]
-                         // or m) then out [M][ldo]; 2 = out^T [N][ldvt]; head size 128, more than
-                         // 256 rows, the tile kernel without split only (gemm_tile_unsplit_blocks)
+                         // or m) then out [M][ldo]; 2 = out^T [N][ldvt]; head size 128, more than 4
+                         // rows, no split (gemm_qkv_fused)
   EPI_DECODE_QKV = 5     // bf16, M <= 4 (decode rows, row m = sample m), head size 128: kind bit 0 =
                          // rotate-half RoPE at pos[m], bit 1 = row m goes to the cache slot
                          // out + (m * kv_cap + pos[m]) * ldo instead of out + m * ldo
@@ -65,12 +69,14 @@ struct GemmArgs {
   const float2* rope;
   const int32_t* pos;
   int64_t ldvt;
-  int kv_cap;  // EPI_DECODE_QKV: cache slots per sample
+  int kv_cap;  // EPI_DECODE_QKV, EPI_QKV_BF16 with out2: cache slots per sample
+  const int32_t* row_sample;  // EPI_QKV_BF16 with out2: sample of each packed row (null: row = sample)
 };
 
-// Blocks of the launch when launch_gemm_bf16 would run these groups through
-// the tile kernel without split-K (the condition of EPI_QKV_BF16), else 0.
-int gemm_tile_unsplit_blocks(const GemmArgs& a, int split_max);
+// Whether launch_gemm_bf16 takes these groups with EPI_QKV_BF16: heads of 128
+// columns, every block with whole sums (the streaming kernel up to 256 rows,
+// the tile kernel where it would not split).
+bool gemm_qkv_fused(const GemmArgs& a, int split_max);
 
 // The rotate-half RoPE of the pair (x0, x1) with (cos, sin): one rounding
 // order shared by every kernel that applies it.
@@ -82,9 +88,6 @@ __device__ __forceinline__ float2 rope_rotate(float x0, float x1, float c, float
 // `split_max` bounds split-K (partial buffers are sized for it).
 hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st);
 hipError_t launch_gemm_f32(GemmArgs& a, int split_max, hipStream_t st);
-
-// Split-K factor the launcher will use for a group of M rows, N columns, K depth.
-int gemm_split_for(int M, int N, int K, bool dual, bool bf16, int split_max);
 
 // Causal attention over packed samples for a compacted list of query rows.
 struct AttnArgs {

@@ -1076,10 +1076,10 @@ struct PrefillRun {
         ga.g[0] = gk;
         ga.g[1] = gv;
       }
-      // Without a cache and with the tile kernel unsplit (many rows), the
-      // GEMM's epilogue applies RoPE and writes bf16 Q, K and V^T itself:
-      // no fp32 round trip and no finalize launch.
-      const bool fused = bf16() && !ck && dh == 128 && gemm_tile_unsplit_blocks(ga, split_cap(2)) > 0;
+      // Where no block takes part of a sum, the GEMM's epilogue applies RoPE,
+      // writes bf16 Q, K and V^T itself and appends keys and values to the
+      // cache: no fp32 round trip, no finalize launch.
+      const bool fused = bf16() && dh == 128 && gemm_qkv_fused(ga, split_cap(2));
       if (fused) {
         ga.epilogue = EPI_QKV_BF16;
         ga.rope = ws.rope;
@@ -1088,10 +1088,15 @@ struct PrefillRun {
         void* outs[3] = {qb, kb, vb};
         const int kinds[3] = {1, 1, 2};
         const int first = ga.ngroups == 3 ? 0 : 1;
+        const int64_t loff = (int64_t)l * kv_B * kv_cap * d;
+        void* cache[3] = {nullptr, ck ? ck + loff : nullptr, ck ? cv + loff : nullptr};
         for (int i = 0; i < ga.ngroups; ++i) {
-          ga.g[i].out = outs[first + i];
+          ga.g[i].out = T.nA > 0 ? outs[first + i] : nullptr;
           ga.g[i].kind = kinds[first + i];
+          ga.g[i].out2 = cache[first + i];
         }
+        ga.kv_cap = kv_cap;
+        ga.row_sample = row_sample;
       }
       {
         ProfScope ps(KC_GEMM_QKV, st);
@@ -1557,12 +1562,28 @@ spider_status run_decode(const spider_decoder_cfg& c, const spider_layer_weights
       ga.g[2].out = cv + loff;
       ga.g[2].kind = 2;
     }
+    const bool qkv_done = !fused && bf16 && dh == 128 && gemm_qkv_fused(ga, std::min(sm, 2));
+    if (qkv_done) {
+      // the same from the GEMM's epilogue: Q to qb, keys and values to the cache
+      ga.epilogue = EPI_QKV_BF16;
+      ga.rope = ws.rope;
+      ga.pos = dlens;
+      ga.kv_cap = kv.cap;
+      void* outs[3] = {qb, nullptr, nullptr};
+      void* cache[3] = {nullptr, ck + loff, cv + loff};
+      const int kinds[3] = {1, 1, 2};
+      for (int i = 0; i < 3; ++i) {
+        ga.g[i].out = outs[i];
+        ga.g[i].out2 = cache[i];
+        ga.g[i].kind = kinds[i];
+      }
+    }
     {
       ProfScope ps(KC_GEMM_QKV, st);
       hipError_t e = gemm(ga, 2);
       SPIDER_REQUIRE(e == hipSuccess, SPIDER_ERR_HIP, "decode gemm_qkv: %s", hipGetErrorString(e));
     }
-    if (!fused) {
+    if (!fused && !qkv_done) {
       ProfScope ps(KC_QKV_FINALIZE, st);
       decode_qkv_kernel<AT><<<dim3((unsigned)B, 3), 256, 0, st>>>(p.Pq, p.Pk, p.Pv, ga.split, ps_, d, dh, dlens,
                                                                    ws.rope, qb, ck, cv, loff, kv.cap);
