@@ -20,7 +20,7 @@
 // the consumer kernel in fixed order: deterministic without atomics), or the
 // fused SwiGLU silu(A Wg^T) * (A Wu^T) rounded to bf16 (dual weights, no split).
 //
-// fp32 path (gemm_f32_kernel): 16x16 FMA tiles through LDS with the same
+// fp32 path (gemm_f32_kernel): 16x16 or 32x32 FMA tiles through LDS with the same
 // group/gather/split/epilogue semantics (used by fp32 workloads).
 #include <algorithm>
 #include <type_traits>
@@ -1300,48 +1300,95 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemmArgs a) {
 }
 
 // ------------------------------------------------------------------ fp32
-template <bool DUAL>
+// 16 R x 16 R outputs per block, R x R per thread, k in chunks of 64 through LDS
+// (the next chunk's loads in flight behind the FMAs); every output adds its k
+// in ascending order.  A small problem is one latency per chunk, so chunks of 64
+// instead of 16 (K = 128: 9.5 -> 4 us a launch); R = 2 halves the LDS reads per FMA
+// where the grid still covers the CUs.
+template <bool DUAL, int R>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs a) {
-  constexpr int T = 16;
-  __shared__ float sA[T][T + 1];
-  __shared__ float sB[T][T + 1];
-  __shared__ float sB2[DUAL ? T : 1][T + 1];
+  constexpr int T = 16 * R, KC = 64, PITCH = KC + 4;
+  __shared__ __attribute__((aligned(16))) float sA[T][PITCH];
+  __shared__ __attribute__((aligned(16))) float sB[DUAL ? 2 * T : T][PITCH];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const TileCoord tc = decode_tile(a, blockIdx.x, T, T);
   const GroupView G = group_view(a, tc.gi);
   if (tc.m0 >= G.M) return;  // a device row count below the launch's bound
-  const int kbeg = tc.s * a.k_per_split;
-  const int kend = min(a.K, kbeg + a.k_per_split);
-  const int m = tc.m0 + ty, n = tc.n0 + tx;
-  const float* A = reinterpret_cast<const float*>(G.A);
-  const float* W = reinterpret_cast<const float*>(G.W);
-  const float* W2 = reinterpret_cast<const float*>(G.W2);
-  // A tile row loaded by this thread: row tc.m0 + ty, column k0 + tx
-  const int am = tc.m0 + ty;
-  const float* arow = nullptr;
-  if (am < G.M) arow = A + (int64_t)(G.rows ? G.rows[am] : am) * a.lda;
-  const int bn = tc.n0 + ty;
-  float acc = 0.f, acc2 = 0.f;
-  for (int k0 = kbeg; k0 < kend; k0 += T) {
-    const int k = k0 + tx;
-    sA[ty][tx] = (arow && k < kend) ? arow[k] : 0.f;
-    sB[ty][tx] = (bn < G.N && k < kend) ? W[(int64_t)bn * a.K + k] : 0.f;
-    if constexpr (DUAL) sB2[ty][tx] = (bn < G.N && k < kend) ? W2[(int64_t)bn * a.K + k] : 0.f;
+  const int K = a.K;
+  // rows ty, ty + 16, .. of the tile, elements tx + 16 e of a chunk
+  const float* pa[R];
+  const float* pb[DUAL ? 2 * R : R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int m = min(tc.m0 + ty + 16 * r, G.M - 1), n = min(tc.n0 + ty + 16 * r, G.N - 1);
+    pa[r] = reinterpret_cast<const float*>(G.A) + (int64_t)(G.rows ? G.rows[m] : m) * a.lda;
+    pb[r] = reinterpret_cast<const float*>(G.W) + (int64_t)n * K;
+    if constexpr (DUAL) pb[R + r] = reinterpret_cast<const float*>(G.W2) + (int64_t)n * K;
+  }
+  constexpr int NB = DUAL ? 2 * R : R;
+  float ra[R][4], rb[NB][4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = k0 + tx + 16 * e;
+      const bool in = k < K;
+      const int kk = in ? k : 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) ra[r][e] = in ? pa[r][kk] : 0.f;
+#pragma unroll
+      for (int r = 0; r < NB; ++r) rb[r][e] = in ? pb[r][kk] : 0.f;
+    }
+  };
+  float acc[R][R] = {}, acc2[DUAL ? R : 1][R] = {};
+  load(0);
+  for (int k0 = 0; k0 < K; k0 += KC) {
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < T; ++kk) {
-      acc = fmaf(sA[ty][kk], sB[tx][kk], acc);
-      if constexpr (DUAL) acc2 = fmaf(sA[ty][kk], sB2[tx][kk], acc2);
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) sA[ty + 16 * r][tx + 16 * e] = ra[r][e];
+#pragma unroll
+      for (int r = 0; r < NB; ++r) sB[ty + 16 * r][tx + 16 * e] = rb[r][e];
     }
     __syncthreads();
-  }
-  if (m < G.M && n < G.N) {
-    if constexpr (DUAL) {
-      reinterpret_cast<float*>(G.out)[(int64_t)m * G.ldo + n] = silu(acc) * acc2;
+    if (k0 + KC < K) load(k0 + KC);
+    const int kn = min(KC, K - k0);
+    auto step = [&](int kk) {
+      floatx4 x[R], w[NB];
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[r] = *reinterpret_cast<const floatx4*>(&sA[ty + 16 * r][kk]);
+#pragma unroll
+      for (int r = 0; r < NB; ++r) w[r] = *reinterpret_cast<const floatx4*>(&sB[tx + 16 * r][kk]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (kk + e >= kn) break;  // K not a multiple of 4: no extra terms
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+          for (int j = 0; j < R; ++j) {
+            acc[i][j] = fmaf(x[i][e], w[j][e], acc[i][j]);
+            if constexpr (DUAL) acc2[i][j] = fmaf(x[i][e], w[R + j][e], acc2[i][j]);
+          }
+      }
+    };
+    if (kn == KC) {
+#pragma unroll 4
+      for (int kk = 0; kk < KC; kk += 4) step(kk);
     } else {
-      reinterpret_cast<float*>(G.out)[tc.s * G.sstride + (int64_t)m * G.ldo + n] = acc;
+      for (int kk = 0; kk < kn; kk += 4) step(kk);
     }
   }
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const int m = tc.m0 + ty + 16 * i, n = tc.n0 + tx + 16 * j;
+      if (m >= G.M || n >= G.N) continue;
+      if constexpr (DUAL)
+        reinterpret_cast<float*>(G.out)[(int64_t)m * G.ldo + n] = silu(acc[i][j]) * acc2[i][j];
+      else
+        reinterpret_cast<float*>(G.out)[tc.s * G.sstride + (int64_t)m * G.ldo + n] = acc[i][j];
+    }
 }
 
 constexpr int kTargetBlocks = 256;
@@ -1702,18 +1749,28 @@ hipError_t launch_gemm_f32(GemmArgs& a, int split_max, hipStream_t st) {
   if (a.epilogue != EPI_PARTIAL_F32 && a.epilogue != EPI_SWIGLU) return hipErrorInvalidValue;
   a.split = 1;
   a.k_per_split = a.K;
+  // 32 x 32 tiles once there are two of them per CU
+  int big = 0;
+  for (int i = 0; i < a.ngroups; ++i) big += ceil_div(a.g[i].M, 32) * ceil_div(a.g[i].N, 32);
+  const int T = big >= 512 ? 32 : 16;
   int t = 0;
   for (int i = 0; i < a.ngroups; ++i) {
     GemmGroup& g = a.g[i];
-    g.tiles_m = ceil_div(g.M, 16);
-    g.tiles_n = ceil_div(g.N, 16);
+    g.tiles_m = ceil_div(g.M, T);
+    g.tiles_n = ceil_div(g.N, T);
     g.tile_begin = t;
     t += g.tiles_m * g.tiles_n;
   }
   a.total_tiles = t;
   if (t == 0) return hipSuccess;
-  if (a.epilogue == EPI_SWIGLU) gemm_f32_kernel<true><<<t, 256, 0, st>>>(a);
-  else gemm_f32_kernel<false><<<t, 256, 0, st>>>(a);
+  const bool dual = a.epilogue == EPI_SWIGLU;
+  if (T == 32) {
+    if (dual) gemm_f32_kernel<true, 2><<<t, 256, 0, st>>>(a);
+    else gemm_f32_kernel<false, 2><<<t, 256, 0, st>>>(a);
+  } else {
+    if (dual) gemm_f32_kernel<true, 1><<<t, 256, 0, st>>>(a);
+    else gemm_f32_kernel<false, 1><<<t, 256, 0, st>>>(a);
+  }
   return hipGetLastError();
 }
 

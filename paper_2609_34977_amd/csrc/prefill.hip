@@ -36,6 +36,8 @@ template <>
 struct Act<float> {
   __device__ static inline void store(float* p, float v) { *p = v; }
   __device__ static inline float load(const float* p) { return *p; }
+  // 4 consecutive values (fp32 inputs may be aligned to 4 bytes only)
+  __device__ static inline float4 load4(const float* p) { return make_float4(p[0], p[1], p[2], p[3]); }
   // 4 consecutive values, p 16-byte aligned
   __device__ static inline void store4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
 };
@@ -44,30 +46,64 @@ struct Act<uint16_t> {
   __device__ static inline void store(uint16_t* p, float v) { *p = f32_to_bf16_bits(v); }
   __device__ static inline float load(const uint16_t* p) { return bf16_bits_to_f32(*p); }
   // 4 consecutive values, p 8-byte aligned
+  __device__ static inline float4 load4(const uint16_t* p) {
+    const uint2 v = *reinterpret_cast<const uint2*>(p);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xFFFF0000u));
+  }
+  // 4 consecutive values, p 8-byte aligned
   __device__ static inline void store4(uint16_t* p, float4 v) {
     *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)f32_to_bf16_bits(v.x) | ((uint32_t)f32_to_bf16_bits(v.y) << 16),
                                               (uint32_t)f32_to_bf16_bits(v.z) | ((uint32_t)f32_to_bf16_bits(v.w) << 16));
   }
 };
 
-// h = float(x)
-template <typename AT>
-__global__ void __launch_bounds__(256) embed_kernel(const AT* __restrict__ x, float* __restrict__ h,
-                                                    int64_t total) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < total) h[i] = Act<AT>::load(x + i);
+// cos/sin table for RoPE: tab[p*half + i] = (cos, sin)(p * theta^(-2i/dh)), double
+// math, of positions 0..n_pos-1, or of list[0..n_pos-1] where a list is given.
+struct RopeArgs {
+  float2* tab;
+  const int32_t* list;
+  int n_pos, half, dh;
+  double log2_theta;
+  int blocks() const { return (int)(((int64_t)n_pos * half + 255) / 256); }
+};
+
+__device__ __forceinline__ void rope_entry(const RopeArgs& r, int64_t t) {
+  if (t >= (int64_t)r.n_pos * r.half) return;
+  const int q = (int)(t / r.half), i = (int)(t % r.half);
+  const int p = r.list ? r.list[q] : q;
+  const double inv = exp2(-(2.0 * i / r.dh) * r.log2_theta);
+  const double ang = (double)p * inv;
+  r.tab[(int64_t)p * r.half + i] = make_float2((float)cos(ang), (float)sin(ang));
 }
 
-// cos/sin table for RoPE: tab[p*half + i] = (cos, sin)(p * theta^(-2i/dh)), double math.
-__global__ void __launch_bounds__(256) rope_table_kernel(float2* __restrict__ tab, int max_pos,
-                                                         int half, int dh, double log2_theta) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (int64_t)max_pos * half) return;
-  const int p = (int)(t / half), i = (int)(t % half);
-  const double inv = exp2(-(2.0 * i / dh) * log2_theta);
-  const double ang = (double)p * inv;
-  tab[t] = make_float2((float)cos(ang), (float)sin(ang));
+// Blocks [0, rope.blocks()) fill the RoPE table, the rest copy h = float(x), four
+// values per thread (total a multiple of 4).
+template <typename AT>
+__global__ void __launch_bounds__(256) embed_kernel(const AT* __restrict__ x, float* __restrict__ h, int64_t total,
+                                                    RopeArgs rope, int rope_blocks) {
+  if ((int)blockIdx.x < rope_blocks) {
+    rope_entry(rope, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    return;
+  }
+  const int64_t i = 4 * ((int64_t)(blockIdx.x - rope_blocks) * 256 + threadIdx.x);
+  if (i < total) *reinterpret_cast<float4*>(h + i) = Act<AT>::load4(x + i);
 }
+
+template <typename AT>
+void launch_embed(const void* x, float* h, int64_t total, const RopeArgs& rope, hipStream_t st) {
+  const int rb = rope.blocks();
+  embed_kernel<AT><<<(unsigned)(rb + (total / 4 + 255) / 256), 256, 0, st>>>(reinterpret_cast<const AT*>(x), h, total,
+                                                                             rope, rb);
+}
+
+// The first norm of a prefill also starts it: the rows of h are read from the
+// input x instead (and written), and blocks past the rows fill the RoPE table.
+template <typename AT>
+struct Begin {
+  const AT* x = nullptr;  // null: h holds the rows
+  RopeArgs rope{};
+};
 
 // One block per row: apply pending residual partials (h[r] += sum_s P[s][pslot[r]],
 // summed in split order) then, if the row is selected,
@@ -79,9 +115,13 @@ __global__ void __launch_bounds__(256) norm_kernel(float* __restrict__ h, int d,
                                                    int64_t pstride, const int32_t* __restrict__ pslot,
                                                    const float* __restrict__ w, float eps,
                                                    const int32_t* __restrict__ nslot, int all_rows,
-                                                   AT* __restrict__ out) {
+                                                   AT* __restrict__ out, Begin<AT> begin, int R) {
   __shared__ float red[4];
   const int r = blockIdx.x;
+  if (r >= R) {
+    rope_entry(begin.rope, (int64_t)(r - R) * 256 + threadIdx.x);
+    return;
+  }
   const int d4 = d >> 2;
   // the row of h and the norm weights first: neither depends on the slot
   // lookups, so their latency overlaps those and the partial sums' (w is
@@ -92,12 +132,15 @@ __global__ void __launch_bounds__(256) norm_kernel(float* __restrict__ h, int d,
 #pragma unroll
   for (int k = 0; k < MAXV; ++k) {
     const int c = threadIdx.x + k * 256;
-    v[k] = c < d4 ? hr[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (begin.x)
+      v[k] = c < d4 ? Act<AT>::load4(begin.x + (int64_t)r * d + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    else
+      v[k] = c < d4 ? hr[c] : make_float4(0.f, 0.f, 0.f, 0.f);
     ww[k] = (w && c < d4) ? w4[c] : make_float4(0.f, 0.f, 0.f, 0.f);  // no weights: residual only
   }
   const int ps = (P && pslot) ? pslot[r] : -1;
   const int ns = all_rows ? r : (nslot ? nslot[r] : -1);
-  if (ps < 0 && ns < 0) return;
+  if (ps < 0 && ns < 0 && !begin.x) return;
   if (ps >= 0) {
     const float4* pr = reinterpret_cast<const float4*>(P + (int64_t)ps * d);
     const int64_t ps4 = pstride >> 2;
@@ -123,6 +166,8 @@ __global__ void __launch_bounds__(256) norm_kernel(float* __restrict__ h, int d,
           v[k].w += add[q][k].w;
         }
     }
+  }
+  if (ps >= 0 || begin.x) {
 #pragma unroll
     for (int k = 0; k < MAXV; ++k) {
       const int c = threadIdx.x + k * 256;
@@ -153,11 +198,12 @@ __global__ void __launch_bounds__(256) norm_kernel(float* __restrict__ h, int d,
 template <typename AT>
 void launch_norm(int R, float* h, int d, const float* P, int psplit, int64_t pstride,
                  const int32_t* pslot, const float* w, float eps, const int32_t* nslot,
-                 int all_rows, AT* out, hipStream_t st) {
+                 int all_rows, AT* out, hipStream_t st, const Begin<AT>& begin = Begin<AT>{}) {
+  const int grid = R + (begin.x ? begin.rope.blocks() : 0);
   if (d <= 4096)
-    norm_kernel<AT, 4><<<R, 256, 0, st>>>(h, d, P, psplit, pstride, pslot, w, eps, nslot, all_rows, out);
+    norm_kernel<AT, 4><<<grid, 256, 0, st>>>(h, d, P, psplit, pstride, pslot, w, eps, nslot, all_rows, out, begin, R);
   else
-    norm_kernel<AT, 8><<<R, 256, 0, st>>>(h, d, P, psplit, pstride, pslot, w, eps, nslot, all_rows, out);
+    norm_kernel<AT, 8><<<grid, 256, 0, st>>>(h, d, P, psplit, pstride, pslot, w, eps, nslot, all_rows, out, begin, R);
 }
 
 // Blocks [0, nq): Q rows, [nq, nq+R): K rows; then V.  Sums split partials,
@@ -415,30 +461,60 @@ __global__ void __launch_bounds__(256) decode_attention_kernel(const AT* __restr
   const int cg = tid % nv, kg = tid / nv;
   uint4 vpre[PF];
 #pragma unroll
-  for (int u = 0; u < PF; ++u) {
-    const int j = kg + u * ng;
-    vpre[u] = (kg < ng && j < n) ? reinterpret_cast<const uint4*>(vb + (int64_t)j * d)[cg] : make_uint4(0, 0, 0, 0);
-  }
+  for (int u = 0; u < PF; ++u)
+    vpre[u] = reinterpret_cast<const uint4*>(vb + (int64_t)min(kg + u * ng, n - 1) * d)[cg];
   float mx = -INFINITY;
-  for (int j = tid; j < n; j += 256) {
-    const uint4* kr = reinterpret_cast<const uint4*>(kb + (int64_t)j * d);
-    float acc = 0.f;
-    for (int q0 = 0; q0 < nv; q0 += 16) {  // 16 vectors (256 B) of the row in flight
-      uint4 kv[16];
+  if ((nv & (nv - 1)) == 0 && nv <= 64) {
+    // Scores: the nv lanes that hold a key's row between them (a whole row per
+    // group: coalesced, eight rows in flight), their partial sums added by a
+    // butterfly.  A thread per key instead reads a row's vectors one by one
+    // from its own line: 23 us for 8 samples of 40 heads and 280 keys, 12 now.
+    float qv[VE];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) kv[u] = q0 + u < nv ? kr[q0 + u] : make_uint4(0, 0, 0, 0);
+    for (int e = 0; e < VE; ++e) qv[e] = qs[cg * VE + e];
+    for (int j0 = kg; j0 < n; j0 += 8 * ng) {
+      uint4 kv[8];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        if (q0 + u >= nv) break;
+      for (int u = 0; u < 8; ++u) kv[u] = reinterpret_cast<const uint4*>(kb + (int64_t)min(j0 + u * ng, n - 1) * d)[cg];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
         float x[VE];
         unpack16<AT>(kv[u], x);
+        float acc = 0.f;
 #pragma unroll
-        for (int e = 0; e < VE; ++e) acc = fmaf(qs[(q0 + u) * VE + e], x[e], acc);
+        for (int e = 0; e < VE; ++e) acc = fmaf(qv[e], x[e], acc);
+        if (nv == 16) acc = row16_sum(acc);
+        else
+          for (int o = nv >> 1; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
+        const int j = j0 + u * ng;
+        if (j < n) {
+          const float v = acc * scale;
+          if (cg == 0) z[j] = v;
+          mx = fmaxf(mx, v);
+        }
       }
     }
-    const float v = acc * scale;
-    z[j] = v;
-    mx = fmaxf(mx, v);
+  } else {
+    for (int j = tid; j < n; j += 256) {
+      const uint4* kr = reinterpret_cast<const uint4*>(kb + (int64_t)j * d);
+      float acc = 0.f;
+      for (int q0 = 0; q0 < nv; q0 += 16) {  // 16 vectors (256 B) of the row in flight
+        uint4 kv[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) kv[u] = q0 + u < nv ? kr[q0 + u] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          if (q0 + u >= nv) break;
+          float x[VE];
+          unpack16<AT>(kv[u], x);
+#pragma unroll
+          for (int e = 0; e < VE; ++e) acc = fmaf(qs[(q0 + u) * VE + e], x[e], acc);
+        }
+      }
+      const float v = acc * scale;
+      z[j] = v;
+      mx = fmaxf(mx, v);
+    }
   }
   mx = wave_max(mx);
   if (lane == 0) red[wave] = mx;
@@ -502,29 +578,38 @@ __global__ void __launch_bounds__(256) decode_attention_kernel(const AT* __restr
 }
 
 // One block per row: logits = the split partials summed in order; the arg max
-// (ties to the lowest id) by a per-thread scan in id order and a fixed tree.
-__global__ void __launch_bounds__(256) logits_argmax_kernel(const float* __restrict__ P, int split, int64_t pstride,
-                                                            int V, float* __restrict__ logits,
-                                                            int32_t* __restrict__ next) {
-  __shared__ float bv[256];
-  __shared__ int bi[256];
+// (ties to the lowest id) by a per-thread scan in id order, then within the waves
+// and across them.
+constexpr int kArgmaxThreads = 1024;
+__global__ void __launch_bounds__(kArgmaxThreads) logits_argmax_kernel(const float* __restrict__ P, int split,
+                                                                       int64_t pstride, int V,
+                                                                       float* __restrict__ logits,
+                                                                       int32_t* __restrict__ next) {
+  __shared__ float bv[kArgmaxThreads / 64];
+  __shared__ int bi[kArgmaxThreads / 64];
   const int b = blockIdx.x, tid = threadIdx.x;
   float best = -INFINITY;
   int arg = 0x7fffffff;
   if (split == 1 && V % 4 == 0) {
-    // float4 pieces 4t, 4t + 1024, ...: four in flight, ids still ascending per thread
+    // float4 pieces tid, tid + 1024, ...: eight in flight, ids still ascending per thread
     const float4* P4 = reinterpret_cast<const float4*>(P + (int64_t)b * V);
     const int V4 = V / 4;
-    for (int v0 = tid; v0 < V4; v0 += 1024) {
-      float4 x[4];
+    for (int v0 = tid; v0 < V4; v0 += 8 * kArgmaxThreads) {
+      float4 x[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (v0 + 256 * u < V4) x[u] = P4[v0 + 256 * u];
+      for (int u = 0; u < 8; ++u) x[u] = P4[min(v0 + kArgmaxThreads * u, V4 - 1)];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int v4 = v0 + 256 * u;
+      for (int u = 0; u < 8; ++u) {
+        const int v4 = v0 + kArgmaxThreads * u;
         if (v4 >= V4) break;
-        if (logits) reinterpret_cast<float4*>(logits + (int64_t)b * V)[v4] = x[u];
+        // (the caller's logits need not be 16-byte aligned)
+        if (logits) {
+          float* o = logits + (int64_t)b * V + 4 * (int64_t)v4;
+          o[0] = x[u].x;
+          o[1] = x[u].y;
+          o[2] = x[u].z;
+          o[3] = x[u].w;
+        }
         const float e[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -535,7 +620,7 @@ __global__ void __launch_bounds__(256) logits_argmax_kernel(const float* __restr
       }
     }
   } else {
-    for (int v = tid; v < V; v += 256) {
+    for (int v = tid; v < V; v += kArgmaxThreads) {
       float x = 0.f;
       for (int s = 0; s < split; ++s) x += P[s * pstride + (int64_t)b * V + v];
       if (logits) logits[(int64_t)b * V + v] = x;
@@ -545,21 +630,28 @@ __global__ void __launch_bounds__(256) logits_argmax_kernel(const float* __restr
       }
     }
   }
-  bv[tid] = best;
-  bi[tid] = arg;
-  __syncthreads();
-  for (int o = 128; o >= 1; o >>= 1) {
-    if (tid < o) {
-      const float x = bv[tid + o];
-      const int i = bi[tid + o];
-      if (x > bv[tid] || (x == bv[tid] && i < bi[tid])) {
-        bv[tid] = x;
-        bi[tid] = i;
-      }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const float x = __shfl_xor(best, o, 64);
+    const int i = __shfl_xor(arg, o, 64);
+    if (x > best || (x == best && i < arg)) {
+      best = x;
+      arg = i;
     }
-    __syncthreads();
   }
-  if (tid == 0 && next) next[b] = bi[0];
+  if ((tid & 63) == 0) {
+    bv[tid >> 6] = best;
+    bi[tid >> 6] = arg;
+  }
+  __syncthreads();
+  if (tid == 0 && next) {
+    for (int w = 1; w < kArgmaxThreads / 64; ++w)
+      if (bv[w] > best || (bv[w] == best && bi[w] < arg)) {
+        best = bv[w];
+        arg = bi[w];
+      }
+    next[b] = arg;
+  }
 }
 
 // Index of this thread among the block's threads with `on` set (thread
@@ -977,6 +1069,7 @@ struct PrefillRun {
   const int32_t* dstart;  // [R] first row of the sample that owns each row
   int R, max_s;
   hipStream_t st;
+  Begin<AT> first{};  // deferred start of the call
   int pend_split = 0;
   int64_t pend_stride = 0;  // elements between the pending partial slabs
   const int32_t* pend_slot = nullptr;
@@ -1004,33 +1097,35 @@ struct PrefillRun {
     return bf16() ? launch_gemm_bf16(ga, sm, st) : launch_gemm_f32(ga, sm, st);
   }
 
-  // RoPE table and h = x
-  spider_status begin(const void* x) {
+  // RoPE table and h = x, by the first norm (defer) or by a launch of their own
+  spider_status begin(const void* x, bool defer) {
     const int half = c.d / c.H / 2, dh = c.d / c.H;
-    {
-      const int64_t n = (int64_t)max_s * half;
-      rope_table_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(ws.rope, max_s, half, dh,
-                                                                    std::log2((double)c.theta));
-      SPIDER_LAUNCHED("rope_table");
+    const RopeArgs rope{ws.rope, nullptr, max_s, half, dh, std::log2((double)c.theta)};
+    if (defer) {
+      first.x = reinterpret_cast<const AT*>(x);
+      first.rope = rope;
+      return SPIDER_OK;
     }
-    {
-      ProfScope ps(KC_EMBED, st);
-      const int64_t n = (int64_t)R * c.d;
-      embed_kernel<AT><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(reinterpret_cast<const AT*>(x), h, n);
-      SPIDER_LAUNCHED("embed");
-    }
+    ProfScope ps(KC_EMBED, st);
+    launch_embed<AT>(x, h, (int64_t)R * c.d, rope, st);
+    SPIDER_LAUNCHED("embed");
     return SPIDER_OK;
+  }
+
+  // one norm launch over the pending residual partials (and the deferred start)
+  void norm(const float* w, float eps, const int32_t* nslot, int all_rows, AT* out) {
+    launch_norm<AT>(R, h, c.d, ws.Pres, pend_split, pend_stride, pend_slot, w, eps, nslot, all_rows, out, st, first);
+    pend_split = 0;
+    pend_slot = nullptr;
+    first = Begin<AT>{};
   }
 
   // adds the pending residual partials to h
   spider_status flush() {
-    if (pend_split == 0) return SPIDER_OK;
+    if (pend_split == 0 && !first.x) return SPIDER_OK;
     ProfScope ps(KC_RESIDUAL, st);
-    launch_norm<AT>(R, h, c.d, ws.Pres, pend_split, pend_stride, pend_slot, nullptr, 0.f, nullptr, 0,
-                    static_cast<AT*>(nullptr), st);
+    norm(nullptr, 0.f, nullptr, 0, static_cast<AT*>(nullptr));
     SPIDER_LAUNCHED("residual_add");
-    pend_split = 0;
-    pend_slot = nullptr;
     return SPIDER_OK;
   }
 
@@ -1053,11 +1148,8 @@ struct PrefillRun {
     if (T.nA > 0 || ck) {
       {
         ProfScope ps(KC_RMSNORM, st);
-        launch_norm<AT>(R, h, d, ws.Pres, pend_split, pend_stride, pend_slot, w.attn_norm, c.eps, nullptr, 1,
-                        xn, st);
+        norm(w.attn_norm, c.eps, nullptr, 1, xn);
         SPIDER_LAUNCHED("rmsnorm(attn)");
-        pend_split = 0;
-        pend_slot = nullptr;
       }
       GemmArgs ga{};
       ga.K = d;
@@ -1146,11 +1238,8 @@ struct PrefillRun {
     if (T.nF > 0) {
       {
         ProfScope ps(KC_RMSNORM, st);
-        launch_norm<AT>(R, h, d, ws.Pres, pend_split, pend_stride, pend_slot, w.ffn_norm, c.eps,
-                        tab + T.offSlotF, 0, xn, st);
+        norm(w.ffn_norm, c.eps, tab + T.offSlotF, 0, xn);
         SPIDER_LAUNCHED("rmsnorm(ffn)");
-        pend_split = 0;
-        pend_slot = nullptr;
       }
       GemmArgs gu{};
       gu.ngroups = 1;
@@ -1230,7 +1319,7 @@ spider_status run_prefill(const spider_decoder_cfg& c, const spider_layer_weight
     run.kv_B = B;
     run.row_sample = ws.tables + 2 * R;
   }
-  SPIDER_TRY(run.begin(x));
+  SPIDER_TRY(run.begin(x, true));
   for (int l = 0; l < c.L; ++l) SPIDER_TRY(run.layer(l, lt[l]));
   return run.flush();
 }
@@ -1305,7 +1394,7 @@ spider_status run_prefill_online(const spider_decoder_cfg& c, const spider_layer
   SPIDER_TRY(upload_ints(fixed.data(), fixed.size(), ows.tab, st));
 
   PrefillRun<AT> run{c, W, h, ows.p, ows.tab, ows.tab + ot.pos, ows.tab + ot.start, R, max_s, st};
-  SPIDER_TRY(run.begin(x));
+  SPIDER_TRY(run.begin(x, false));  // the controller reads h before the first norm
   SPIDER_HIP(launch_fill_zero(ows.acc, (size_t)R * sizeof(double), st));
   if (s_sa_out && Wn > 0) SPIDER_HIP(launch_fill_zero(s_sa_out, (size_t)Wn * R * sizeof(float), st));
 
@@ -1490,25 +1579,17 @@ spider_status run_decode(const spider_decoder_cfg& c, const spider_layer_weights
   const int d = c.d, dh = d / c.H, half = dh / 2;
   const PrefillWs& p = ws.p;
   std::vector<int32_t> tab(2 * B);
-  int max_pos = 0;
   for (int b = 0; b < B; ++b) {
     tab[b] = b;
     tab[B + b] = lens[b];
-    max_pos = std::max(max_pos, lens[b]);
   }
   SPIDER_TRY(upload_ints(tab.data(), tab.size(), ws.tab, st));
   const int32_t* ident = ws.tab;
   const int32_t* dlens = ws.tab + B;
   {
-    const int64_t n = (int64_t)(max_pos + 1) * half;
-    rope_table_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(ws.rope, max_pos + 1, half, dh,
-                                                                  std::log2((double)c.theta));
-    SPIDER_LAUNCHED("rope_table");
-  }
-  {
     ProfScope ps(KC_EMBED, st);
-    const int64_t n = (int64_t)B * d;
-    embed_kernel<AT><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(reinterpret_cast<const AT*>(x), h, n);
+    // RoPE table rows of the new tokens' positions only
+    launch_embed<AT>(x, h, (int64_t)B * d, RopeArgs{ws.rope, dlens, B, half, dh, std::log2((double)c.theta)}, st);
     SPIDER_LAUNCHED("embed");
   }
   AT* xn = reinterpret_cast<AT*>(p.xn);
@@ -1665,7 +1746,7 @@ spider_status run_decode(const spider_decoder_cfg& c, const spider_layer_weights
     }
     hipError_t e = bf16 ? launch_gemm_bf16(gh, kHeadSplit, st) : launch_gemm_f32(gh, kHeadSplit, st);
     SPIDER_REQUIRE(e == hipSuccess, SPIDER_ERR_HIP, "lm head: %s", hipGetErrorString(e));
-    logits_argmax_kernel<<<B, 256, 0, st>>>(ws.Plog, gh.split, (int64_t)B * V, V, logits, next);
+    logits_argmax_kernel<<<B, kArgmaxThreads, 0, st>>>(ws.Plog, gh.split, (int64_t)B * V, V, logits, next);
     SPIDER_LAUNCHED("logits_argmax");
   }
   return SPIDER_OK;
