@@ -738,16 +738,17 @@ template <int MH, bool DUAL, bool QKV = false>
 __global__ void __launch_bounds__(256) gemm_tile_kernel(GemmArgs a) {
   constexpr int KB = 64;
   constexpr int BM = 64 * MH;
-  constexpr int A_BYTES = BM * 128;
-  constexpr int STAGE_BYTES = A_BYTES + 256 * 128;
+  constexpr int A_BYTES = BM * 128, W_BYTES = 256 * 128;
+  constexpr int WST = MH <= 3 ? 3 : 2;  // weight stages (activations: two)
   constexpr int OPITCH = 136;  // dual epilogue: bf16 tile BM x 128, padded rows
-  constexpr int RING_BYTES = 2 * STAGE_BYTES > BM * OPITCH * 2 ? 2 * STAGE_BYTES : BM * OPITCH * 2;
+  constexpr int STAGES_BYTES = 2 * A_BYTES + WST * W_BYTES;
+  constexpr int RING_BYTES = STAGES_BYTES > BM * OPITCH * 2 ? STAGES_BYTES : BM * OPITCH * 2;
   // QKV epilogue: RoPE positions of the block's rows past the ring.  They
   // share its LDS array on purpose: with a second __shared__ object the
   // compiler can no longer tell the fragment reads from the in-flight
   // global_load_lds writes and waits for all loads before them.
   constexpr int POS_BYTES = QKV ? BM * 4 : 0;
-  static_assert(RING_BYTES + POS_BYTES <= 144 * 1024, "LDS of one block");
+  static_assert(RING_BYTES + POS_BYTES <= 145 * 1024, "LDS of one block");
   constexpr int A_PER_WAVE = BM / 32;  // DMA instructions (8 rows each) per wave and k-block
   __shared__ __attribute__((aligned(1024))) uint8_t ring[RING_BYTES + POS_BYTES];
 
@@ -834,18 +835,17 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(GemmArgs a) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) acc[i][u] = floatx16{};
 
-  // DMA instruction p (of NP per wave and k-block) of k-block kb into stage S
-  constexpr int NP = A_PER_WAVE + 8;
+  // DMA of this wave: piece p of the activations of k-block kb into activation
+  // stage S, of the weights into weight stage S
   // LDS offset of the ring (the DMA takes its LDS destination from M0)
   const uint32_t ring_lds = lds_offset(ring);
-  auto issue_piece = [&](int kb, auto S, auto Pc) {
-    constexpr int st = decltype(S)::value;
-    constexpr int p = decltype(Pc)::value;
-    const uint32_t base = ring_lds + st * STAGE_BYTES;
-    if constexpr (p < A_PER_WAVE)
-      dma16(pa[p] + kb * KB, base + (wave * A_PER_WAVE + p) * 1024);
-    else
-      dma16(pw[p - A_PER_WAVE] + kb * KB, base + A_BYTES + (8 * wave + p - A_PER_WAVE) * 1024);
+  auto issue_a = [&](int kb, auto S, auto Pc) {
+    constexpr int st = decltype(S)::value, p = decltype(Pc)::value;
+    dma16(pa[p] + kb * KB, ring_lds + st * A_BYTES + (wave * A_PER_WAVE + p) * 1024);
+  };
+  auto issue_w = [&](int kb, auto S, auto Pc) {
+    constexpr int st = decltype(S)::value, p = decltype(Pc)::value;
+    dma16(pw[p] + kb * KB, ring_lds + 2 * A_BYTES + st * W_BYTES + (8 * wave + p) * 1024);
   };
 
   // weight tile u of the wave: LDS weight rows wrow(u) .. +31
@@ -854,16 +854,10 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(GemmArgs a) {
     else return 128 * nh + 32 * u;
   };
 
-  // MMAs of the k-block in stage S.  The DMA of k-block kbn into stage SN is
-  // issued between the MMA groups of the first two k-steps (a burst of all of
-  // them at once stalls the wave before its MMAs; spread over all four k-steps
-  // the last ones land too late), measured 10-15 % faster than either.
-  // fragments of k-step q of the k-block in stage S
-  auto frags = [&](auto S, int q, bf16x8 (&w)[4], bf16x8 (&x)[MH]) __attribute__((always_inline)) {
-    constexpr int st = decltype(S)::value;
-    const uint8_t* tile = ring + st * STAGE_BYTES;
-    const uint8_t* at = tile + (32 * MH * mh + lo) * 128;
-    const uint8_t* wt = tile + A_BYTES + lo * 128;
+  // fragments of k-step q of the k-block in activation stage SA, weight stage SW
+  auto frags = [&](auto SA, auto SW, int q, bf16x8 (&w)[4], bf16x8 (&x)[MH]) __attribute__((always_inline)) {
+    const uint8_t* at = ring + decltype(SA)::value * A_BYTES + (32 * MH * mh + lo) * 128;
+    const uint8_t* wt = ring + 2 * A_BYTES + decltype(SW)::value * W_BYTES + lo * 128;
     const int c = 16 * ((4 * hi + q) ^ swz(lo));
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -873,18 +867,30 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(GemmArgs a) {
       x[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(at + i * 32 * 128 + c));
   };
   bf16x8 wf[2][4], af[2][MH];
-  constexpr int HALF = NP / 2;  // DMA pieces issued in step 3, the rest in the next step 0
+  // activation pieces of the next k-block issued in step 3 (the rest in the next step 0)
+  constexpr int AH = WST == 2 ? A_PER_WAVE : A_PER_WAVE / 2;
 
-  // One k-block in stage S.  On entry buffer 0 holds its step-0 fragments and
-  // the first half of the DMA of the next k-block (stage SN) is in flight.
-  // Step 0 issues the other half; the barrier comes after step 2's MMAs, once
-  // step 3's fragments are in registers: then stage S is free (DMA of k-block
-  // kdma goes there, interleaved with step 3's MMAs) and stage SN has landed
-  // (the next k-block's step-0 fragments are read while step 3's MMAs run).
-  auto kblock = [&](auto S, auto SN, int knext, int kdma, auto FULL) __attribute__((always_inline)) {
-    auto mmas = [&](auto Q, auto P0, auto P1, auto SD, int kd) __attribute__((always_inline)) {
-      constexpr int q = decltype(Q)::value;
-      constexpr int p0 = decltype(P0)::value, p1 = decltype(P1)::value;
+  // One k-block kb in stages SA, SW.  On entry buffer 0 holds its step-0 fragments.
+  // The barrier comes after step 2's MMAs, once step 3's fragments are in
+  // registers: then its stages are free and k-block kb + 1 has landed (its step-0
+  // fragments are read while step 3's MMAs run).  DMAs are issued between the
+  // MMAs of a step: a burst stalls the wave.
+  //  two weight stages (256-row tiles, whose stages fill the LDS): step 3 brings
+  //    the activations of k-block kb + 2, the next step 0 its weights, and the
+  //    barrier waits for all of them;
+  //  three: the activations of kb + 2 in step 3 and the next step 0, the weights of
+  //    kb + 2 in steps 1 and 2 of kb, still in flight across the barrier: they have
+  //    a k-block longer to arrive.  Measured against two stages: 192-row tiles,
+  //    down at 6014 rows 480 -> 422 us, QKV at 705 rows 101 -> 91; 128-row tiles,
+  //    gate/up at 384 rows 90 -> 73.
+  auto kblock = [&](auto SA, auto SW, int k1, int k2, auto FULL) __attribute__((always_inline)) {
+    constexpr int sa = decltype(SA)::value, sw = decltype(SW)::value;
+    using SA1 = std::integral_constant<int, 1 - sa>;
+    using SW1 = std::integral_constant<int, (sw + 1) % WST>;
+    using SW2 = std::integral_constant<int, (sw + 2) % WST>;
+    // MMAs of step Q with n DMA pieces spread between their row tiles
+    auto mmas = [&](auto Q, auto N, auto piece) __attribute__((always_inline)) {
+      constexpr int q = decltype(Q)::value, n = decltype(N)::value;
       static_for<0, MH>([&](auto I) {
         constexpr int i = I.value;
         if (decltype(FULL)::value || i < live) {
@@ -892,45 +898,70 @@ __global__ void __launch_bounds__(256) gemm_tile_kernel(GemmArgs a) {
           for (int u = 0; u < 4; ++u)
             acc[i][u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[q & 1][u], af[q & 1][i], acc[i][u], 0, 0, 0);
         }
-        constexpr int a0 = p0 + i * (p1 - p0) / MH, a1 = p0 + (i + 1) * (p1 - p0) / MH;
-        static_for<a0, a1>([&](auto P) { issue_piece(kd, SD, P); });
+        static_for<i * n / MH, (i + 1) * n / MH>(piece);
         __builtin_amdgcn_sched_barrier(0);
       });
     };
-    using Z = std::integral_constant<int, 0>;
-    frags(S, 1, wf[1], af[1]);
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    auto none = [&](auto) {};
+    constexpr int AL = A_PER_WAVE - AH;  // 0 with two weight stages
+    frags(SA, SW, 1, wf[1], af[1]);
     __builtin_amdgcn_sched_barrier(0);
-    mmas(std::integral_constant<int, 0>{}, std::integral_constant<int, HALF>{}, std::integral_constant<int, NP>{}, SN, knext);
-    frags(S, 2, wf[0], af[0]);
+    mmas(I0{}, std::integral_constant<int, WST == 2 ? 8 : AL>{}, [&](auto P) __attribute__((always_inline)) {
+      if constexpr (WST == 3) issue_a(k1, SA1{}, std::integral_constant<int, AH + P.value>{});
+      else issue_w(k1, SW1{}, P);
+    });
+    frags(SA, SW, 2, wf[0], af[0]);
     __builtin_amdgcn_sched_barrier(0);
-    mmas(std::integral_constant<int, 1>{}, Z{}, Z{}, SN, knext);
-    frags(S, 3, wf[1], af[1]);
+    if constexpr (WST == 2) mmas(I1{}, I0{}, none);
+    else mmas(I1{}, std::integral_constant<int, 4>{}, [&](auto P) __attribute__((always_inline)) { issue_w(k2, SW2{}, P); });
+    frags(SA, SW, 3, wf[1], af[1]);
     __builtin_amdgcn_sched_barrier(0);
-    mmas(std::integral_constant<int, 2>{}, Z{}, Z{}, SN, knext);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    frags(SN, 0, wf[0], af[0]);
+    if constexpr (WST == 2) {
+      mmas(I2{}, I0{}, none);
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    } else {
+      mmas(I2{}, std::integral_constant<int, 4>{}, [&](auto P) __attribute__((always_inline)) {
+        issue_w(k2, SW2{}, std::integral_constant<int, 4 + P.value>{});
+      });
+      asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+    frags(SA1{}, SW1{}, 0, wf[0], af[0]);
     __builtin_amdgcn_sched_barrier(0);
-    mmas(std::integral_constant<int, 3>{}, Z{}, std::integral_constant<int, HALF>{}, S, kdma);
+    mmas(I3{}, std::integral_constant<int, AH>{}, [&](auto P) __attribute__((always_inline)) { issue_a(k2, SA, P); });
   };
 
   if (nkb > 0) {
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, 1>;
-    static_for<0, NP>([&](auto P) { issue_piece(0, S0{}, P); });
+    const int k1 = min(1, nkb - 1);
+    static_for<0, A_PER_WAVE>([&](auto P) { issue_a(0, S0{}, P); });
+    static_for<0, 8>([&](auto P) { issue_w(0, S0{}, P); });
     dma_wait_barrier();
-    frags(S0{}, 0, wf[0], af[0]);
-    static_for<0, HALF>([&](auto P) { issue_piece(min(1, nkb - 1), S1{}, P); });
+    frags(S0{}, S0{}, 0, wf[0], af[0]);
+    if constexpr (WST == 3) static_for<0, 8>([&](auto P) { issue_w(k1, S1{}, P); });
+    static_for<0, AH>([&](auto P) { issue_a(k1, S1{}, P); });
     // Waves whose row tiles all hold rows < M (every block but the last row
     // tile) run a copy of the loop without the per-tile guards: a branch
     // inside the MMA groups splits the loop into basic blocks, across which
     // the compiler can only wait for every outstanding LDS read.
     auto run = [&](auto FULL) __attribute__((always_inline)) {
+      constexpr int UN = WST == 2 ? 2 : 6;  // stages repeat after UN k-blocks
       int kb = 0;
-      for (; kb + 2 <= nkb; kb += 2) {
-        kblock(S0{}, S1{}, min(kb + 1, nkb - 1), min(kb + 2, nkb - 1), FULL);
-        kblock(S1{}, S0{}, min(kb + 2, nkb - 1), min(kb + 3, nkb - 1), FULL);
-      }
-      if (kb < nkb) kblock(S0{}, S1{}, min(kb + 1, nkb - 1), min(kb + 2, nkb - 1), FULL);
+      for (; kb + UN <= nkb; kb += UN)
+        static_for<0, UN>([&](auto J) __attribute__((always_inline)) {
+          kblock(std::integral_constant<int, J.value % 2>{}, std::integral_constant<int, J.value % WST>{},
+                 min(kb + J.value + 1, nkb - 1), min(kb + J.value + 2, nkb - 1), FULL);
+        });
+      const int rem = nkb - kb;
+      static_for<0, UN - 1>([&](auto J) __attribute__((always_inline)) {
+        if (J.value < rem)
+          kblock(std::integral_constant<int, J.value % 2>{}, std::integral_constant<int, J.value % WST>{},
+                 min(kb + J.value + 1, nkb - 1), min(kb + J.value + 2, nkb - 1), FULL);
+      });
     };
     if (live == MH) run(std::true_type{});
     else run(std::false_type{});
@@ -1497,8 +1528,10 @@ bool stream_fits(const GemmArgs& a, int maxM, bool dual) {
 // More than 256 rows: gemm_tile_kernel when the shapes fit it (N a multiple of
 // the block's output columns, K of 64, 16-byte aligned bf16 output rows for
 // the SwiGLU epilogue).  The row tile (256, 192 or 128) minimises the number
-// of waves of blocks (one block per CU) times the cost of a block; split-K
-// only fills a grid that would leave CUs idle.
+// of waves of blocks (one block per CU) times the cost of a block, measured per
+// wave at K = 5120: 140, 97 and about 80 us (320 : 240 : 190 leans to the larger
+// tiles, which read less in launches of many waves); split-K only fills a grid
+// that would leave CUs idle.
 bool tile_path_fits(const GemmArgs& a, bool dual) {
   if (a.K % 64) return false;
   for (int i = 0; i < a.ngroups; ++i) {
@@ -1525,7 +1558,8 @@ TileChoice tile_choice(const GemmArgs& a, int split_max, bool dual) {
     const int bm = 64 * mh;
     const int tiles = tiles_for(a, bm, bn);
     const int split = dual ? 1 : choose_split(tiles, a.K, split_max, 64, true);
-    double cost = (double)ceil_div(tiles * split, kTargetBlocks) * (bm + 64) / split;
+    const double block = mh == 4 ? 320 : (mh == 3 ? 240 : 190);
+    double cost = (double)ceil_div(tiles * split, kTargetBlocks) * block / split;
     int tail = 0, ts = 0;
     // SwiGLU, one group: a last wave at most a quarter full is split along k
     // into pieces that run beside the first wave (fp32 partials in scratch)
@@ -1535,7 +1569,7 @@ TileChoice tile_choice(const GemmArgs& a, int split_max, bool dual) {
       int s = std::min(16, std::min(nkb / 2, kTargetBlocks / r));
       while (s >= 2 && (size_t)r * s * bm * 256 * 4 > a.scratch_bytes) --s;
       if (s >= 2) {
-        const double c2 = (double)(tiles / kTargetBlocks) * (bm + 64) + (bm + 64) * (1.0 / s + 0.1);
+        const double c2 = (double)(tiles / kTargetBlocks) * block + block * (1.0 / s + 0.1);
         if (c2 < cost) {
           cost = c2;
           tail = r;

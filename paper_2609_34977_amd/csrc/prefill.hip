@@ -1192,7 +1192,22 @@ struct PrefillRun {
       }
       {
         ProfScope ps(KC_GEMM_QKV, st);
-        hipError_t e = gemm(ga, 2);
+        hipError_t e = hipSuccess;
+        if (fused && T.nA > 4 && T.nA <= 256 && R > 256) {
+          // few queries among many rows (only the text rows, say): as tiles beside
+          // those of the keys and values they cost a wave of blocks of their own;
+          // the streaming kernel takes them in the time of their weights (256 of
+          // 6014 rows: 437 us in one launch, 412 in two)
+          GemmArgs gq = ga;
+          gq.ngroups = 1;
+          e = gemm(gq, 2);
+          ga.ngroups = 2;
+          ga.g[0] = ga.g[1];
+          ga.g[1] = ga.g[2];
+          if (e == hipSuccess) e = gemm(ga, 2);
+        } else {
+          e = gemm(ga, 2);
+        }
         SPIDER_REQUIRE(e == hipSuccess, SPIDER_ERR_HIP, "gemm_qkv: %s", hipGetErrorString(e));
       }
       if (!fused) {
