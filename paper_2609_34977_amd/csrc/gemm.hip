@@ -1359,15 +1359,15 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs a) {
   constexpr int NB = DUAL ? 2 * R : R;
   float ra[R][4], rb[NB][4];
   auto load = [&](int k0) {
+    // (past K: any element of the row; the terms are left out below.  A load
+    // under a bounds check of its own would wait for the one before it.)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int k = k0 + tx + 16 * e;
-      const bool in = k < K;
-      const int kk = in ? k : 0;
+      const int k = min(k0 + tx + 16 * e, K - 1);
 #pragma unroll
-      for (int r = 0; r < R; ++r) ra[r][e] = in ? pa[r][kk] : 0.f;
+      for (int r = 0; r < R; ++r) ra[r][e] = pa[r][k];
 #pragma unroll
-      for (int r = 0; r < NB; ++r) rb[r][e] = in ? pb[r][kk] : 0.f;
+      for (int r = 0; r < NB; ++r) rb[r][e] = pb[r][k];
     }
   };
   float acc[R][R] = {}, acc2[DUAL ? R : 1][R] = {};
