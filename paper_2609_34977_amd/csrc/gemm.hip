@@ -17,8 +17,9 @@
 // k-split, m-tile) and the hardware block id is remapped so consecutive
 // logical tiles run on the same XCD (blocks are dispatched round-robin over
 // the 8 XCDs) and share its L2.  Epilogues: fp32 split-K partials (summed by
-// the consumer kernel in fixed order: deterministic without atomics), or the
-// fused SwiGLU silu(A Wg^T) * (A Wu^T) rounded to bf16 (dual weights, no split).
+// the consumer kernel in fixed order: deterministic without atomics), the
+// fused SwiGLU silu(A Wg^T) * (A Wu^T) rounded to bf16 (dual weights, no split),
+// or, unsplit, Q, K and V with their RoPE, scaling and rounding (gemm_qkv_fused).
 //
 // fp32 path (gemm_f32_kernel): 16x16 or 32x32 FMA tiles through LDS with the same
 // group/gather/split/epilogue semantics (used by fp32 workloads).
@@ -711,13 +712,13 @@ __global__ void __launch_bounds__(256) gemm_stream_kernel(GemmArgs a) {
 // no exchange.  Per k-step a wave reads MH + 4 fragments from LDS for 4 MH
 // v_mfma_f32_32x32x16_bf16 (acc[i][t]: row tile i, weight tile t).
 //
-// Operands go global -> LDS by global_load_lds into two stages (BM + 256 rows
-// of 128 B each); chunk c of row r sits in slot c ^ (r & 7) as in the
-// streaming kernel.  The DMA of k-block kb+1 is interleaved with the first
-// half of the MMAs of kb, then the wave waits for all its loads and the block
-// passes one barrier.  What bounds it: operand bytes from L2 (a block tile of
-// 256 x 256 needs 32 B per clock per CU at the MFMA rate; L2 hits measured
-// ~20 B per clock per CU), hence the large tile and the L2-friendly order.
+// Operands go global -> LDS by global_load_lds, rows of 128 B whose 16-byte
+// chunks are permuted by swz(row): two activation stages, and two (256-row
+// tiles) or three weight stages; the order of DMAs, MMAs and the one barrier
+// per k-block is described at kblock below.  What bounds it: operand bytes from
+// L2 (a block tile of 256 x 256 needs 32 B per clock per CU at the MFMA rate;
+// L2 hits measured ~20 B per clock per CU), hence the large tile and the
+// L2-friendly order.
 // Row tiles entirely past M skip their MMAs; their rows read row M-1.
 //
 // Tile order: per group, split-major, then GM = 8 row tiles x all column

@@ -7,8 +7,10 @@
 //   if A_l non-empty:
 //     rmsnorm   every row: h += pending residual partials; xn = bf16(norm(h))
 //     gemm_qkv  one grouped launch: Q over A_l (gathered rows of xn), K and V
-//               over every row (bypassing rows still provide keys/values)
-//     qkv_fin   sum split-K partials, RoPE (table built in double), round
+//               over every row (bypassing rows still provide keys/values), with
+//               RoPE (table built in double) and rounding in its epilogue
+//     qkv_fin   (fp32, few rows or shapes without that epilogue) sum split-K
+//               partials, RoPE, round
 //     attention causal, compacted queries A_l
 //     gemm_o    O rows of A_l -> fp32 split-K partials (pending residual)
 //   if F_l non-empty:
