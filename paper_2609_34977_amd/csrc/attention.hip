@@ -7,7 +7,12 @@
 // 32 queries, head).  The key range of the 32 queries is cut into 32-key
 // blocks aligned to multiples of 32, dealt round-robin to the 4 waves; each
 // wave keeps its own online softmax and the four partial results are merged
-// through LDS in fixed wave order at the end.  S^T = K Q^T is computed with
+// through LDS in fixed wave order at the end, each wave for a quarter of the
+// columns.  A block is one latency chain (192 rows: at most two key blocks per
+// wave): with wave 0 merging all columns, read with bank conflicts, and LDS
+// shuffles for the key range it took 11.5 us at 192 rows and 32 heads, now 10.0.
+// It runs below 128 blocks of attention_wide_kernel; above, that one is faster
+// (705 rows, 32 heads: 26.8 us against 46.6).  S^T = K Q^T is computed with
 // v_mfma_f32_32x32x16_bf16 so that each lane owns one query (lane % 32) and
 // 16 of the 32 keys (the other 16 are in lane ^ 32); the softmax runs per lane
 // in fp32 (exp2 with the 1/sqrt(dh)*log2(e) scale folded in) plus one
@@ -61,8 +66,9 @@ __device__ __forceinline__ void wait_vm() {
 __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs a) {
   constexpr int DH = 128;
   constexpr int NW = 4;
-  __shared__ float xm[NW - 1][32], xl[NW - 1][32];
-  __shared__ __attribute__((aligned(16))) float xo[NW - 1][64 * 64];
+  static_assert(DH == 32 * NW, "wave c merges dh columns [32c, 32c + 32)");
+  __shared__ float xm[NW][32], xl[NW][32];
+  __shared__ floatx4 xo[NW][16][64];  // wave, 4 sums of a lane, lane
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hi = lane >> 5, lo = lane & 31;
   const int h = blockIdx.y;
   const int nq = a.nq_dev ? min(a.nq, *a.nq_dev) : a.nq;
@@ -84,24 +90,13 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs a) {
     qf[t] = __builtin_bit_cast(bf16x8, u);
   }
   // key range of the 32 queries (every block holds at least one query)
-  int lo_row = qstart, hi_row = qrow;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    lo_row = min(lo_row, __shfl_xor(lo_row, o, 64));
-    hi_row = max(hi_row, __shfl_xor(hi_row, o, 64));
-  }
+  const int lo_row = -wave_max_int(-qstart), hi_row = wave_max_int(qrow);
   const int jb0 = lo_row & ~31;
   const int nblk = (hi_row - jb0) / 32 + 1;
   // a key block [j0, j0 + 31] is fully visible to every valid query iff
   // j0 >= st_max and j0 + 31 <= q_min (invalid lanes store nothing)
-  int st_max = qok ? qstart : -1, q_min = qok ? qrow : 0x7FFFFFFF;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    st_max = max(st_max, __shfl_xor(st_max, o, 64));
-    q_min = min(q_min, __shfl_xor(q_min, o, 64));
-  }
-  st_max = __builtin_amdgcn_readfirstlane(st_max);
-  q_min = __builtin_amdgcn_readfirstlane(q_min);
+  const int st_max = __builtin_amdgcn_readfirstlane(wave_max_int(qok ? qstart : -1));
+  const int q_min = __builtin_amdgcn_readfirstlane(-wave_max_int(qok ? -qrow : -0x7FFFFFFF));
   const float sc = a.scale * kLog2e;
   const float lazy = kLazyLog2 / sc;  // in raw score units
   float m_run = -INFINITY, l_run = 0.f;
@@ -211,60 +206,45 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs a) {
       }
   }
 
-  // ---- merge the waves' partial softmax states (fixed order 0..3)
-  if (wave > 0) {
-    if (hi == 0) {
-      xm[wave - 1][lo] = m_run;
-      xl[wave - 1][lo] = l_run;
-    }
-    float* dst = xo[wave - 1] + lane * 64;
-#pragma unroll
-    for (int c = 0; c < DH / 32; ++c)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        *reinterpret_cast<floatx4*>(dst + 16 * c + 4 * v) =
-            floatx4{o[c][4 * v], o[c][4 * v + 1], o[c][4 * v + 2], o[c][4 * v + 3]};
+  // ---- merge the waves' partial softmax states (fixed order 0..3): wave c takes
+  // dh columns [32c, 32c + 32).  Consecutive lanes hold consecutive 16 bytes.
+  if (hi == 0) {
+    xm[wave][lo] = m_run;
+    xl[wave][lo] = l_run;
   }
-  __syncthreads();
-  if (wave != 0 || !qok) return;
-  float M = m_run;
-#pragma unroll
-  for (int w = 0; w < NW - 1; ++w) M = fmaxf(M, xm[w][lo]);
-  const float Msc = M * sc;  // maxima are raw scores; weights exp2((m - M) sc)
-  const float f0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(fmaf(m_run, sc, -Msc));
-  float L = f0 * l_run;
 #pragma unroll
   for (int c = 0; c < DH / 32; ++c)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[c][r] *= f0;
+    for (int v = 0; v < 4; ++v)
+      xo[wave][4 * c + v][lane] = floatx4{o[c][4 * v], o[c][4 * v + 1], o[c][4 * v + 2], o[c][4 * v + 3]};
+  __syncthreads();
+  if (!qok) return;
+  float M = xm[0][lo];
 #pragma unroll
-  for (int w = 0; w < NW - 1; ++w) {
+  for (int w = 1; w < NW; ++w) M = fmaxf(M, xm[w][lo]);
+  const float Msc = M * sc;  // maxima are raw scores; weights exp2((m - M) sc)
+  float L = 0.f;
+  floatx4 sum[4];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
     const float mw = xm[w][lo];
     const float fw = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(fmaf(mw, sc, -Msc));
-    L += fw * xl[w][lo];
-    const float* srcp = xo[w] + lane * 64;
+    L = fmaf(fw, xl[w][lo], L);
 #pragma unroll
-    for (int c = 0; c < DH / 32; ++c)
+    for (int v = 0; v < 4; ++v) {
+      const floatx4 x = xo[w][4 * wave + v][lane];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const floatx4 x = *reinterpret_cast<const floatx4*>(srcp + 16 * c + 4 * v);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[c][4 * v + e] += fw * x[e];
-      }
+      for (int e = 0; e < 4; ++e) sum[v][e] = w == 0 ? x[e] * fw : fmaf(fw, x[e], sum[v][e]);
+    }
   }
   const float inv = L > 0.f ? 1.0f / L : 0.f;
-  uint16_t* O = reinterpret_cast<uint16_t*>(a.o) + (int64_t)qa * a.d + h * DH;
+  uint16_t* O = reinterpret_cast<uint16_t*>(a.o) + (int64_t)qa * a.d + h * DH + 32 * wave + 4 * hi;
 #pragma unroll
-  for (int c = 0; c < DH / 32; ++c)
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      const int dh0 = c * 32 + 8 * r4 + 4 * hi;
-      uint32_t w0 = (uint32_t)f32_to_bf16_bits(o[c][4 * r4] * inv) |
-                    ((uint32_t)f32_to_bf16_bits(o[c][4 * r4 + 1] * inv) << 16);
-      uint32_t w1 = (uint32_t)f32_to_bf16_bits(o[c][4 * r4 + 2] * inv) |
-                    ((uint32_t)f32_to_bf16_bits(o[c][4 * r4 + 3] * inv) << 16);
-      *reinterpret_cast<uint2*>(O + dh0) = make_uint2(w0, w1);
-    }
+  for (int v = 0; v < 4; ++v) {
+    const uint32_t w0 = (uint32_t)f32_to_bf16_bits(sum[v][0] * inv) | ((uint32_t)f32_to_bf16_bits(sum[v][1] * inv) << 16);
+    const uint32_t w1 = (uint32_t)f32_to_bf16_bits(sum[v][2] * inv) | ((uint32_t)f32_to_bf16_bits(sum[v][3] * inv) << 16);
+    *reinterpret_cast<uint2*>(O + 8 * v) = make_uint2(w0, w1);
+  }
 }
 
 // bf16, dh = 128, many queries (attention_wide_kernel): one block of 4 waves

@@ -164,6 +164,17 @@ __device__ __forceinline__ int wave_sum_int(int v) {
   return v + __builtin_amdgcn_update_dpp(v, v, kDppX1, 0xF, 0xF, false);
 }
 
+__device__ __forceinline__ int wave_max_int(int v) {
+  const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = max((int)p[0], (int)p[1]);
+  const auto q = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = max((int)q[0], (int)q[1]);
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, kDppRor8, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, kDppRor4, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, kDppX2, 0xF, 0xF, false));
+  return max(v, __builtin_amdgcn_update_dpp(v, v, kDppX1, 0xF, 0xF, false));
+}
+
 // Order-preserving map of a float to uint32 (-0.0 is mapped like +0.0).
 __device__ __forceinline__ uint32_t float_order_key(float f) {
   if (f == 0.0f) f = 0.0f;
