@@ -37,13 +37,14 @@ import statistics
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 # kernel class -> (source files whose text defines its kernels, pattern of the dispatches
-# that make one launch of the class, pattern of the one dispatch counted per launch)
+# that make one launch of the class, pattern of the one dispatch counted per launch).
+# The stream kernel's third argument is its epilogue: 1 = SwiGLU.
 _GEMM_SRC = ("csrc/gemm.hip", "csrc/kernels.h", "csrc/common.h")
 CLASSES = {
     "gemm_gateup": (_GEMM_SRC,
-                    r"gemm_stream_kernel<\d+, \d+, true\b|gemm_bf16_kernel<\d+, \d+, \d+, \d+, \d+, true"
+                    r"gemm_stream_kernel<\d+, \d+, (?:true|1)\b|gemm_bf16_kernel<\d+, \d+, \d+, \d+, \d+, true"
                     r"|gemm_tile_kernel<\d+, true\b|swiglu_tail_reduce_kernel",
-                    r"gemm_stream_kernel<\d+, \d+, true\b|gemm_bf16_kernel<\d+, \d+, \d+, \d+, \d+, true"
+                    r"gemm_stream_kernel<\d+, \d+, (?:true|1)\b|gemm_bf16_kernel<\d+, \d+, \d+, \d+, \d+, true"
                     r"|gemm_tile_kernel<\d+, true\b"),
 }
 
@@ -267,8 +268,9 @@ _MFMA_GROUPS = [
     (r"gemm_tile_kernel<\d+, true\b", "tile GEMM, SwiGLU epilogue (gate/up, > 256 rows)"),
     (r"gemm_tile_kernel<\d+, false, true>", "tile GEMM, RoPE/bf16 epilogue (QKV, > 256 rows)"),
     (r"gemm_tile_kernel<\d+, false, false>", "tile GEMM, fp32 partials (O and down, > 256 rows)"),
-    (r"gemm_stream_kernel<\d+, \d+, true", "streaming GEMM, SwiGLU (<= 256 rows)"),
-    (r"gemm_stream_kernel<\d+, \d+, false", "streaming GEMM, fp32 partials (<= 256 rows)"),
+    (r"gemm_stream_kernel<\d+, \d+, 1>", "streaming GEMM, SwiGLU (<= 256 rows)"),
+    (r"gemm_stream_kernel<\d+, \d+, 3>", "streaming GEMM, RoPE/bf16 epilogue (QKV, <= 256 rows)"),
+    (r"gemm_stream_kernel<\d+, \d+, 0>", "streaming GEMM, fp32 partials (<= 256 rows)"),
     (r"attention_wide_kernel", "attention, many queries"),
     (r"attention_bf16_kernel", "attention, few queries"),
 ]
