@@ -1752,12 +1752,9 @@ hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
     }
     return hipGetLastError();
   }
-  // Shapes the streaming and tile kernels do not take go to the LDS-staged
-  // kernel: non-dual up to 256 rows a tile of all rows, otherwise 128-row tiles
-  // (the SwiGLU launch up to 256 rows always fits the streaming kernel: K and N
-  // are multiples of 64 and its output is aligned)
-  const int BM = maxM <= 256 && !dual ? std::max(64, (maxM + 63) / 64 * 64) : 128;
-  const int BN = dual || maxM <= 256 ? 64 : 128;
+  // Shapes the tile kernel does not take (past 256 rows; K and N are multiples of
+  // 64 and the outputs aligned, so the streaming kernel takes the rest)
+  const int BM = 128, BN = dual ? 64 : 128;
   for (int i = 0; i < a.ngroups; ++i)
     if (a.g[i].N % BN) return hipErrorInvalidValue;
   if (a.K % 32) return hipErrorInvalidValue;
@@ -1765,17 +1762,8 @@ hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
   a.k_per_split = ceil_div(a.K / 32, a.split) * 32;
   fill_tiles(a, BM, BN);
   if (a.total_tiles == 0) return hipSuccess;
-  if (dual) {
-    launch_cfg<128, 64, 2, 2, true>(a, st);
-  } else {
-    switch (BM * 1000 + BN) {
-      case 64064: launch_cfg<64, 64, 2, 2, false>(a, st); break;
-      case 128064: launch_cfg<128, 64, 2, 2, false>(a, st); break;
-      case 192064: launch_cfg<192, 64, 2, 2, false>(a, st); break;
-      case 256064: launch_cfg<256, 64, 2, 2, false>(a, st); break;
-      default: launch_cfg<128, 128, 2, 2, false>(a, st); break;
-    }
-  }
+  if (dual) launch_cfg<128, 64, 2, 2, true>(a, st);
+  else launch_cfg<128, 128, 2, 2, false>(a, st);
   return hipGetLastError();
 }
 
