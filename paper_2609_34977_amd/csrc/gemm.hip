@@ -1549,12 +1549,12 @@ bool tile_path_fits(const GemmArgs& a, bool dual) {
 
 struct TileChoice {
   int mh, split, tail, tail_split;
+  double cost;
 };
 
 TileChoice tile_choice(const GemmArgs& a, int split_max, bool dual) {
   const int bn = dual ? 128 : 256;
-  TileChoice best{4, 1, 0, 0};
-  double best_cost = 1e300;
+  TileChoice best{4, 1, 0, 0, 1e300};
   for (int mh : {4, 3, 2}) {
     const int bm = 64 * mh;
     const int tiles = tiles_for(a, bm, bn);
@@ -1578,10 +1578,7 @@ TileChoice tile_choice(const GemmArgs& a, int split_max, bool dual) {
         }
       }
     }
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = TileChoice{mh, split, tail, ts};
-    }
+    if (cost < best.cost) best = TileChoice{mh, split, tail, ts, cost};
   }
   return best;
 }
@@ -1591,7 +1588,6 @@ hipError_t launch_tile(GemmArgs& a, int split_max, bool dual, hipStream_t st) {
   const TileChoice tc = tile_choice(a, split_max, dual);
   const int best_mh = tc.mh, best_split = tc.split, best_tail = tc.tail, best_ts = tc.tail_split;
   const bool qkv = a.epilogue == EPI_QKV_BF16;
-  if (qkv && best_split != 1) return hipErrorInvalidValue;
   a.split = best_split;
   a.k_per_split = ceil_div(a.K / 64, a.split) * 64;
   fill_tiles(a, 64 * best_mh, bn);
@@ -1691,6 +1687,28 @@ bool gemm_qkv_fused(const GemmArgs& a, int split_max) {
   return !has_row_count(a) && tile_path_fits(a, false) && tile_choice(a, split_max, false).split == 1;
 }
 
+// Few queries (only the text rows, say) beside many keys and values: as tiles of
+// the same launch they may open a wave of blocks of their own, alone the
+// streaming kernel takes them in 24 us (up to 64 rows, d = 4096).  Q goes apart
+// where it has one 64-row step and the launch without it is a wave cheaper.  The
+// line is measured, QKV per layer in one launch and in two, d = 4096: 64 queries of
+// 1921 rows 153 and 141 us, of 4417 291 and 285, of 5953 365 and 365, of 6144 409 and
+// 374; 128 queries of 2945 rows 203 and 205, of 5953 366 and 373; 192 of 1921 153
+// and 156, of 6144 412 and 389; 256 of 6014 372 and 391.  A wave costs 190 to 320 here and
+// less in truth (its few blocks have the chip to themselves), hence the margin:
+// without it (every size) 64 queries of 2049 rows took 174 us for 152.  Both launches
+// run unsplit, whatever split the keys and values alone would have taken.
+bool gemm_qkv_q_apart(const GemmArgs& a, int split_max) {
+  constexpr double kQCost = 140;
+  if (a.ngroups != 3 || a.g[0].M <= 4 || a.g[0].M > 64 || max_rows(a) <= 256 || !gemm_qkv_fused(a, split_max))
+    return false;
+  GemmArgs kv = a;
+  kv.ngroups = 2;
+  kv.g[0] = a.g[1];
+  kv.g[1] = a.g[2];
+  return tile_choice(kv, 1, false).cost + kQCost < tile_choice(a, 1, false).cost;
+}
+
 hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
   const int maxM = max_rows(a);
   if (a.epilogue == EPI_LENS_STATS) {
@@ -1707,8 +1725,10 @@ hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
   const bool dual = a.epilogue == EPI_SWIGLU;
   const bool gemv_ok = gemv_fits(maxM, a.K);
   if (a.epilogue == EPI_QKV_BF16) {
-    // whole sums in one block, whole heads, 16-byte stores
-    if (!gemm_qkv_fused(a, split_max) || !a.rope || !a.pos) return hipErrorInvalidValue;
+    // whole sums in one block, whole heads, 16-byte stores.  (Whether a split
+    // would pay is the caller's question to gemm_qkv_fused, of all groups; this may
+    // be some of them.)
+    if (!gemm_qkv_fused(a, 1) || !a.rope || !a.pos) return hipErrorInvalidValue;
     for (int i = 0; i < a.ngroups; ++i) {
       const GemmGroup& g = a.g[i];
       if (reinterpret_cast<uintptr_t>(g.out) % 16 || reinterpret_cast<uintptr_t>(g.out2) % 16 || g.ldo % 8 ||
@@ -1716,7 +1736,7 @@ hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
         return hipErrorInvalidValue;
       if (g.kind == 2 && g.out && (a.ldvt % 32 || a.ldvt < g.M)) return hipErrorInvalidValue;
     }
-    if (maxM > 256) return launch_tile(a, split_max, false, st);
+    if (maxM > 256) return launch_tile(a, 1, false, st);
     a.split = 1;
     a.k_per_split = a.K;
     fill_tiles(a, 256, 64);

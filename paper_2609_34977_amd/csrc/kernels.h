@@ -78,6 +78,10 @@ struct GemmArgs {
 // the tile kernel where it would not split).
 bool gemm_qkv_fused(const GemmArgs& a, int split_max);
 
+// Whether three groups that gemm_qkv_fused takes run faster as two launches: group
+// 0 (the queries) alone, then groups 1 and 2.
+bool gemm_qkv_q_apart(const GemmArgs& a, int split_max);
+
 // The rotate-half RoPE of the pair (x0, x1) with (cos, sin): one rounding
 // order shared by every kernel that applies it.
 __device__ __forceinline__ float2 rope_rotate(float x0, float x1, float c, float s) {

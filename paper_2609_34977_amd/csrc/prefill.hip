@@ -1174,6 +1174,7 @@ struct PrefillRun {
       // writes bf16 Q, K and V^T itself and appends keys and values to the
       // cache: no fp32 round trip, no finalize launch.
       const bool fused = bf16() && dh == 128 && gemm_qkv_fused(ga, split_cap(2));
+      const bool q_apart = fused && gemm_qkv_q_apart(ga, split_cap(2));
       if (fused) {
         ga.epilogue = EPI_QKV_BF16;
         ga.rope = ws.rope;
@@ -1195,11 +1196,7 @@ struct PrefillRun {
       {
         ProfScope ps(KC_GEMM_QKV, st);
         hipError_t e = hipSuccess;
-        if (fused && T.nA > 4 && T.nA <= 256 && R > 256) {
-          // few queries among many rows (only the text rows, say): as tiles beside
-          // those of the keys and values they cost a wave of blocks of their own;
-          // the streaming kernel takes them in the time of their weights (256 of
-          // 6014 rows: 437 us in one launch, 412 in two)
+        if (q_apart) {
           GemmArgs gq = ga;
           gq.ngroups = 1;
           e = gemm(gq, 2);

@@ -4,8 +4,8 @@
   (the lanes of a key in the decode attention are not a power of two), GEMMs whose K is no
   multiple of 4 and of 64, and the 32 x 32 tiles of many outputs;
 * more than 256 rows with four to ten k-blocks (fewer than the large tile's stages are deep
-  on one side, a split of them on the other), and few queries among them, whose Q projection
-  leaves the launch of K and V;
+  on one side, a split of them on the other), and few queries among them (in the fused launch
+  at 420 rows, through split partials at 1100);
 * decode steps of 6 and of 33 samples (QKV finished in the GEMM's epilogue, one and more
   row tiles) and of 260, at a width outside
   the fused epilogues' tiles (partials and decode_qkv);
