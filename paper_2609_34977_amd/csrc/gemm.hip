@@ -1689,24 +1689,25 @@ bool gemm_qkv_fused(const GemmArgs& a, int split_max) {
 
 // Few queries (only the text rows, say) beside many keys and values: as tiles of
 // the same launch they may open a wave of blocks of their own, alone the
-// streaming kernel takes them in 24 us (up to 64 rows, d = 4096).  Q goes apart
-// where it has one 64-row step and the launch without it is a wave cheaper.  The
-// line is measured, QKV per layer in one launch and in two, d = 4096: 64 queries of
-// 1921 rows 153 and 141 us, of 4417 291 and 285, of 5953 365 and 365, of 6144 409 and
-// 374; 128 queries of 2945 rows 203 and 205, of 5953 366 and 373; 192 of 1921 153
-// and 156, of 6144 412 and 389; 256 of 6014 372 and 391.  A wave costs 190 to 320 here and
-// less in truth (its few blocks have the chip to themselves), hence the margin:
-// without it (every size) 64 queries of 2049 rows took 174 us for 152.  Both launches
-// run unsplit, whatever split the keys and values alone would have taken.
+// streaming kernel takes them in 24 us (64 rows, d = 4096) to 46 us (256).  Q goes
+// apart up to two 64-row steps of it, where the launch without it is enough
+// cheaper.  The line is measured, QKV per layer in one launch and in two, d = 4096:
+// 64 queries of 1921 rows 153 and 141 us, of 4417 291 and 285, of 5953 365 and 365, of
+// 6144 409 and 374; 128 of 2945 rows 203 and 205 (not apart), of 4417 291 and 291, of
+// 6144 411 and 381; 192 of 4417 290 and 301, of 6144 412 and 389; 256 of 6014 372 and 391.
+// A wave costs 190 to 320 here and less in truth (its few blocks have the chip to
+// themselves), hence the margin: 64 queries of 2049 rows take 152 us in one launch, 174
+// in two.  Both launches run unsplit, whatever split the keys and values alone
+// would have taken.
 bool gemm_qkv_q_apart(const GemmArgs& a, int split_max) {
-  constexpr double kQCost = 140;
-  if (a.ngroups != 3 || a.g[0].M <= 4 || a.g[0].M > 64 || max_rows(a) <= 256 || !gemm_qkv_fused(a, split_max))
+  if (a.ngroups != 3 || a.g[0].M <= 4 || a.g[0].M > 128 || max_rows(a) <= 256 || !gemm_qkv_fused(a, split_max))
     return false;
   GemmArgs kv = a;
   kv.ngroups = 2;
   kv.g[0] = a.g[1];
   kv.g[1] = a.g[2];
-  return tile_choice(kv, 1, false).cost + kQCost < tile_choice(a, 1, false).cost;
+  const double q_cost = 100 + 40 * ceil_div(a.g[0].M, 64);
+  return tile_choice(kv, 1, false).cost + q_cost < tile_choice(a, 1, false).cost;
 }
 
 hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
