@@ -540,9 +540,11 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_wide_kernel(At
 // groups added in order through LDS.  (A key at a time with a wave sum each is
 // a chain of one load and one reduction per key: 34 us for 48 queries of 4
 // heads, 7 us now.)  dh not a multiple of 4 keeps single elements.
-__global__ void __launch_bounds__(64) attention_f32_kernel(AttnArgs a) {
-  extern __shared__ float sc[];  // [max_seq]
-  __shared__ __attribute__((aligned(16))) float qs[256], part[256];
+// LDS: sc the scores [max_seq]; the query and the groups' sums beside them, or,
+// where the scores of the longest sample fill the LDS (LONG), the query from
+// memory and the sums over the scores: same arithmetic, same bits.
+template <bool LONG>
+__device__ __forceinline__ void attention_f32_query(const AttnArgs& a, float* sc, float* qs, float* part) {
   const int lane = threadIdx.x;
   const int qa = blockIdx.x, h = blockIdx.y;
   if (a.nq_dev && qa >= *a.nq_dev) return;
@@ -554,8 +556,11 @@ __global__ void __launch_bounds__(64) attention_f32_kernel(AttnArgs a) {
   const float* Vp = reinterpret_cast<const float*>(a.v) + (int64_t)st * a.d + h * dh;
   float* O = reinterpret_cast<float*>(a.o) + (int64_t)qa * a.d + h * dh;
   const bool v4 = dh % 4 == 0;  // rows are 16-byte aligned then (d is a multiple of 4)
-  for (int c = lane; c < dh; c += 64) qs[c] = Q[c];
-  __syncthreads();
+  if constexpr (!LONG) {
+    for (int c = lane; c < dh; c += 64) qs[c] = Q[c];
+    __syncthreads();
+  }
+  const float* q = LONG ? Q : qs;
   float mx = -INFINITY;
   for (int j = lane; j < nk; j += 64) {
     const float* kr = Kp + (int64_t)j * a.d;
@@ -569,15 +574,15 @@ __global__ void __launch_bounds__(64) attention_f32_kernel(AttnArgs a) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           if (c0 + 4 * u >= dh) break;
-          const float4 q = *reinterpret_cast<const float4*>(qs + c0 + 4 * u);
-          dot = fmaf(q.x, x[u].x, dot);
-          dot = fmaf(q.y, x[u].y, dot);
-          dot = fmaf(q.z, x[u].z, dot);
-          dot = fmaf(q.w, x[u].w, dot);
+          const float4 qv = *reinterpret_cast<const float4*>(q + c0 + 4 * u);
+          dot = fmaf(qv.x, x[u].x, dot);
+          dot = fmaf(qv.y, x[u].y, dot);
+          dot = fmaf(qv.z, x[u].z, dot);
+          dot = fmaf(qv.w, x[u].w, dot);
         }
       }
     } else {
-      for (int c = 0; c < dh; ++c) dot = fmaf(qs[c], kr[c], dot);
+      for (int c = 0; c < dh; ++c) dot = fmaf(q[c], kr[c], dot);
     }
     dot *= a.scale;
     sc[j] = dot;
@@ -613,8 +618,9 @@ __global__ void __launch_bounds__(64) attention_f32_kernel(AttnArgs a) {
           o.w = fmaf(p, x[u].w, o.w);
         }
       }
-      *reinterpret_cast<float4*>(part + kg * dh + 4 * cg) = o;  // ng * dh <= 256
     }
+    if constexpr (LONG) __syncthreads();  // the scores are read
+    if (kg < ng) *reinterpret_cast<float4*>(part + kg * dh + 4 * cg) = o;  // ng * dh <= 256
     __syncthreads();
     for (int c = lane; c < dh; c += 64) {
       float v = part[c];
@@ -628,6 +634,20 @@ __global__ void __launch_bounds__(64) attention_f32_kernel(AttnArgs a) {
     for (int j = 0; j < nk; ++j) v = fmaf(sc[j], Vp[(int64_t)j * a.d + c], v);
     O[c] = v / sum;
   }
+}
+
+constexpr int kLdsBytes = 160 * 1024, kF32Lds = 2 * 256 * 4;
+
+__global__ void __launch_bounds__(64) attention_f32_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float sc[];
+  __shared__ __attribute__((aligned(16))) float qs[256], part[256];
+  attention_f32_query<false>(a, sc, qs, part);
+}
+
+// Samples of 40449 to 40960 rows.
+__global__ void __launch_bounds__(64) attention_f32_long_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float sc[];
+  attention_f32_query<true>(a, sc, nullptr, sc);
 }
 
 }  // namespace
@@ -654,7 +674,9 @@ hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t st) {
 hipError_t launch_attention_f32(const AttnArgs& a, int max_seq, hipStream_t st) {
   if (a.nq == 0) return hipSuccess;
   dim3 grid(a.nq, a.H);
-  attention_f32_kernel<<<grid, 64, (size_t)std::max(1, max_seq) * 4, st>>>(a);
+  const size_t scores = (size_t)std::max(1, max_seq) * 4;
+  if (scores + kF32Lds <= kLdsBytes) attention_f32_kernel<<<grid, 64, scores, st>>>(a);
+  else attention_f32_long_kernel<<<grid, 64, scores, st>>>(a);
   return hipGetLastError();
 }
 
