@@ -80,10 +80,6 @@ class Pipeline:
                 raise ValueError(policy.kind)
         return out
 
-    def _wait_inputs(self):
-        if self.quota_mode == 1:
-            self.inputs_read.synchronize()
-
     def step(self, cls_attn, feats, src, text, policy: SkipPolicy):
         """``src``: visual rows already in the decoder width [G, n, d], or, with a
         projector, the ViT rows it reads [G, n+1, d_v] (row 0 = [CLS])."""
@@ -108,7 +104,8 @@ class Pipeline:
             # every tile keeps n_anchor + min(n_cmp, n - n_anchor) rows: the boundaries are
             # known here, and the host plans and launches the prefill while the device still
             # scores (7B, one tile, 8 layers: 1449 -> 1400 us per step).  As with the copy
-            # below, the inputs have been read by the time step() returns (inputs_read).
+            # below, the inputs have been read by the time step() is left, by an
+            # exception too (inputs_read).
             self.inputs_read.record(torch.cuda.current_stream(self.device))
             per = self.tps * (self.n_anchor + min(self.n_cmp, self.n - self.n_anchor)) + self.n_text
             cu = np.arange(self.B + 1, dtype=np.int32) * np.int32(per)
@@ -116,6 +113,14 @@ class Pipeline:
             self.cu_host.copy_(sel["cu_seqlens"], non_blocking=True)
             torch.cuda.current_stream(self.device).synchronize()
             cu = self.cu_host.numpy().copy()
+        try:
+            out = self._prefill(cu, sel, policy)
+        finally:
+            if self.quota_mode == 1:
+                self.inputs_read.synchronize()
+        return {"score": sc, "select": sel, "cu": cu, **out}
+
+    def _prefill(self, cu, sel, policy: SkipPolicy):
         rows = int(cu[-1])
         if policy.kind == "online":
             V = int(policy.w_unembed.shape[0])
@@ -126,10 +131,8 @@ class Pipeline:
                 self.dec, None, cu, sel["x"][:rows], self.n_text, policy.w_unembed, policy.slc_sel,
                 policy.target, policy.w1, policy.w2, policy.T_skip, s_sa=False, out=self.h[:rows],
                 workspace=self.online_ws, weight_table=self.wtable)
-            self._wait_inputs()
-            return {"score": sc, "select": sel, "cu": cu, "codes": codes, "admit": admit, "h": h}
+            return {"codes": codes, "admit": admit, "h": h}
         codes = self.codes(cu, policy)
         h = _lib.prefill(self.dec, None, cu, sel["x"][:rows], codes, out=self.h[:rows],
                          workspace=self.prefill_ws, weight_table=self.wtable)
-        self._wait_inputs()
-        return {"score": sc, "select": sel, "cu": cu, "codes": codes, "h": h}
+        return {"codes": codes, "h": h}
