@@ -95,7 +95,7 @@ __device__ __forceinline__ GroupView group_view(const GemmArgs& a, int gi) {
   return v;
 }
 
-template <int BM, int BN, int WGM, int WGN, int PF, bool DUAL, bool NT = false>
+template <int BM, int BN, int WGM, int WGN, int PF, bool DUAL>
 __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs a) {
   constexpr int BK = 32, PITCH = BK + 8;
   constexpr int BROWS = DUAL ? 2 * BN : BN;
@@ -164,10 +164,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs a) {
     for (int c = 0; c < A_CH; ++c)
       xa[c] = pa[c] ? *reinterpret_cast<const u32x4*>(pa[c] + ko) : u32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int c = 0; c < B_CH; ++c) {
-      const u32x4* src = reinterpret_cast<const u32x4*>(pb[c] + ko);
-      xb[c] = NT ? __builtin_nontemporal_load(src) : *src;
-    }
+    for (int c = 0; c < B_CH; ++c) xb[c] = *reinterpret_cast<const u32x4*>(pb[c] + ko);
   };
   auto store = [&](int buf, const u32x4 (&xa)[A_CH], const u32x4 (&xb)[B_CH]) {
 #pragma unroll
