@@ -1074,7 +1074,6 @@ size_t score_ws_layout(int G, int n, int d, int n_layers, int K, ScoreWs* w, cha
   char* p_psum = take((size_t)G * NB * L1 * K * d * 4);
   char* p_pcnt = take((size_t)G * NB * K * 4);
   char* p_pm = take((size_t)G * NB * K * 4);
-  take((size_t)G * NB * 4);  // holds nothing now: the workspace keeps its size
   char* p_conv = take((size_t)G * 4);
   char* p_asg = take((size_t)G * n * 4);
   char* p_mu = take((size_t)G * L1 * K * d * 4);
