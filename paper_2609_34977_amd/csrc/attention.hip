@@ -539,7 +539,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_wide_kernel(At
 // four with eight in flight; P V: a lane per four columns and key group, the
 // groups added in order through LDS.  (A key at a time with a wave sum each is
 // a chain of one load and one reduction per key: 34 us for 48 queries of 4
-// heads, 7 us now.)  dh not a multiple of 4 keeps single elements.
+// heads, 5 us now.)  dh not a multiple of 4 keeps single elements.
 // LDS: sc the scores [max_seq]; the query and the groups' sums beside them, or,
 // where the scores of the longest sample fill the LDS (LONG), the query from
 // memory and the sums over the scores: same arithmetic, same bits.

@@ -1332,7 +1332,8 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemmArgs a) {
 // 16 R x 16 R outputs per block, R x R per thread, k in chunks of 64 through LDS
 // (the next chunk's loads in flight behind the FMAs); every output adds its k
 // in ascending order.  A small problem is one latency per chunk, so chunks of 64
-// instead of 16 (K = 128: 9.5 -> 4 us a launch); R = 2 halves the LDS reads per FMA
+// instead of 16 (Q, K, V, O and down of 48 rows, d = 128: 9.5 -> 6.8 us a launch on
+// average); R = 2 halves the LDS reads per FMA
 // where the grid still covers the CUs.
 template <bool DUAL, int R>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs a) {
@@ -1526,10 +1527,14 @@ bool stream_fits(const GemmArgs& a, int maxM, bool dual) {
 // More than 256 rows: gemm_tile_kernel when the shapes fit it (N a multiple of
 // the block's output columns, K of 64, 16-byte aligned bf16 output rows for
 // the SwiGLU epilogue).  The row tile (256, 192 or 128) minimises the number
-// of waves of blocks (one block per CU) times the cost of a block, measured per
-// wave at K = 5120: 140, 97 and about 80 us (320 : 240 : 190 leans to the larger
-// tiles, which read less in launches of many waves); split-K only fills a grid
-// that would leave CUs idle.
+// of waves of blocks (one block per CU) times the cost of a block; split-K only
+// fills a grid that would leave CUs idle.  A full wave at K = 5120 was measured at
+// 140, 97 and about 80 us (320 : 222 : 183).  The costs 320 : 240 : 190 lean to the
+// larger tiles, which read less in launches of many waves.  Measured where the two
+// disagree, one layer, leaned and not: QKV of 3136 rows 722 and 751 us, of 6200
+// 1517 and 1544, of 2350 (d = 5120) 783 and 808; gate/up loses by it at a split
+// last wave: 600 rows 341 and 331, 1400 rows 691 and 678, 1050 (d = 5120) 802 and
+// 782, 6014 rows 2663 and 2656.
 bool tile_path_fits(const GemmArgs& a, bool dual) {
   if (a.K % 64) return false;
   for (int i = 0; i < a.ngroups; ++i) {

@@ -430,19 +430,17 @@ __device__ __forceinline__ void unpack16(const uint4& v, float* x) {
 }
 
 // grid (H, B): one query (the new token) against the cache rows 0..lens[b].
-// Logits fp32 (dot products over c ascending), softmax with the block max,
-// exponentials summed per thread in key order then in a fixed tree; P.V in
-// fp32: thread t sums keys j = g, g + G, ... (g = t / dh, G = 256 / dh) for
-// column t % dh, the G partial sums added in order, one division.
+// Logits fp32: where a row is a power of two of 16-byte vectors (at most 64), a
+// lane per vector and a butterfly over the row's lanes, else a thread per key and
+// c ascending.  Softmax with the block max, exponentials summed per thread in key
+// order then in a fixed tree.  P.V in fp32: a thread per (vector of VE columns,
+// key group g of G = 256 / (vectors per row)) sums keys g, g + G, ..., the G
+// partial sums are added in order, one division.
 template <typename AT>
 __global__ void __launch_bounds__(256) decode_attention_kernel(const AT* __restrict__ Q, const AT* __restrict__ ck,
                                                                const AT* __restrict__ cv, int64_t layer_off, int cap,
                                                                const int32_t* __restrict__ lens, int d, int dh,
                                                                float scale, AT* __restrict__ O) {
-  // One block per (head, sample).  Scores: a thread per cached key, its row
-  // read as 16-byte vectors all in flight (dh <= 256).  P V: a thread per
-  // (group of VE columns, key group), its keys strided by the number of key
-  // groups; the key groups are combined in fixed order through LDS.
   constexpr int VE = 16 / sizeof(AT);  // elements per 16-byte vector
   __shared__ float qs[kDecodeMaxDh];
   __shared__ float z[kDecodeMaxKeys];
@@ -470,7 +468,7 @@ __global__ void __launch_bounds__(256) decode_attention_kernel(const AT* __restr
     // Scores: the nv lanes that hold a key's row between them (a whole row per
     // group: coalesced, eight rows in flight), their partial sums added by a
     // butterfly.  A thread per key instead reads a row's vectors one by one
-    // from its own line: 23 us for 8 samples of 40 heads and 280 keys, 12 now.
+    // from its own line (8 samples of 40 heads and 280 keys: 23 us, 18 now).
     float qv[VE];
 #pragma unroll
     for (int e = 0; e < VE; ++e) qv[e] = qs[cg * VE + e];

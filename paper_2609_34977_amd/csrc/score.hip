@@ -10,11 +10,13 @@
 //   anchor_topk    grid G x 64: one wave finds the n_anchor-th largest score
 //                  bit by bit and writes the ascending anchor and non-anchor
 //                  lists.
-//   anchor_maxsim  m_i = max_p u_i . u_p.  bf16: grid (ceil(n/128), G) x 256,
-//                  v_mfma_f32_32x32x16_bf16 on the raw rows (exact products,
-//                  fp32 accumulation; anchors staged in LDS per 64-dimension
-//                  chunk) scaled by the two inverse norms; fp32: grid
-//                  (ceil(n/4), G), a wave-per-row FMA loop.
+//   anchor_maxsim  m_i = max_p u_i . u_p.  bf16: v_mfma_f32_32x32x16_bf16 on the
+//                  raw rows (exact products, fp32 accumulation) scaled by the two
+//                  inverse norms: grid (ceil(n/32), G) x 256, a wave per anchor
+//                  tile, rows and anchors through an LDS ring (rows32), from 512
+//                  128-row blocks on grid (ceil(n/128), G) x 256, anchors staged
+//                  in LDS per 64-dimension chunk; fp32: grid (ceil(n/4), G), a
+//                  wave-per-row FMA loop.
 //   kmeans         grid (NB, G) x 512 per Lloyd pass: rows and centroids in
 //                  LDS, distances, then per-block cluster sums in a fixed
 //                  order (deterministic).
