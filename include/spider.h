@@ -305,7 +305,8 @@ spider_status spider_plan_skips(int L, int n_vis, const float* s_sa, int s_sa_st
  *   silu(g)*u rounded to bf16 (round-to-nearest-even) from fp32; GEMMs
  *   accumulate in fp32 (MFMA); O and down outputs are added to h in fp32;
  *   softmax in fp32.  Requires dh == 128, d % 64 == 0, d_ff % 64 == 0.
- * dtype SPIDER_F32: everything fp32 (any dh <= 256 with dh even).
+ * dtype SPIDER_F32: everything fp32 (any dh <= 256 with dh even; samples of at
+ *   most 40960 rows in a layer whose attention some row takes).
  * Both: d % 4 == 0, d <= 8192; x (bf16), weights, norms and h_out 16-byte
  * aligned.
  * Inputs: cfg; layers = HOST array [L] of per-layer device weight pointers

@@ -636,7 +636,7 @@ __device__ __forceinline__ void attention_f32_query(const AttnArgs& a, float* sc
   }
 }
 
-constexpr int kLdsBytes = 160 * 1024, kF32Lds = 2 * 256 * 4;
+constexpr int kLdsBytes = 4 * kAttnF32MaxSeq, kF32Lds = 2 * 256 * 4;
 
 __global__ void __launch_bounds__(64) attention_f32_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) float sc[];
@@ -674,6 +674,7 @@ hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t st) {
 hipError_t launch_attention_f32(const AttnArgs& a, int max_seq, hipStream_t st) {
   if (a.nq == 0) return hipSuccess;
   dim3 grid(a.nq, a.H);
+  if (max_seq > kAttnF32MaxSeq) return hipErrorInvalidValue;
   const size_t scores = (size_t)std::max(1, max_seq) * 4;
   if (scores + kF32Lds <= kLdsBytes) attention_f32_kernel<<<grid, 64, scores, st>>>(a);
   else attention_f32_long_kernel<<<grid, 64, scores, st>>>(a);

@@ -107,6 +107,8 @@ struct AttnArgs {
   const int32_t* nq_dev;   // optional device query count: min(nq, *nq_dev) queries (nq = the bound)
 };
 hipError_t launch_attention_bf16(const AttnArgs& a, hipStream_t st);
+// The scores of a query fill the LDS of a CU at the longest fp32 sample.
+constexpr int kAttnF32MaxSeq = 160 * 1024 / 4;
 hipError_t launch_attention_f32(const AttnArgs& a, int max_seq, hipStream_t st);
 
 // Online skip controller (Sec. 4.2.1, Eq. 4, Eq. 6).  Candidates are visual

@@ -1304,6 +1304,13 @@ int fill_positions(int B, const int32_t* cu, int32_t* pos, int32_t* start) {
   return max_s;
 }
 
+// fp32 attention holds the scores of a query in LDS: asked before any launch
+spider_status check_longest(const spider_decoder_cfg& c, int max_s) {
+  SPIDER_REQUIRE(c.dtype == SPIDER_BF16 || max_s <= kAttnF32MaxSeq, SPIDER_ERR_UNSUPPORTED,
+                 "spider_prefill: fp32 samples of at most %d rows, %d given", kAttnF32MaxSeq, max_s);
+  return SPIDER_OK;
+}
+
 template <typename AT>
 spider_status run_prefill(const spider_decoder_cfg& c, const spider_layer_weights* W, int B,
                           const int32_t* cu, const void* x, const uint8_t* codes, float* h,
@@ -1320,7 +1327,10 @@ spider_status run_prefill(const spider_decoder_cfg& c, const spider_layer_weight
       for (int r = cu[b]; r < cu[b + 1]; ++r) tab[2 * R + r] = b;
   std::vector<LayerTables> lt(c.L);
   TableBuilder tb{tab, 0};
-  for (int l = 0; l < c.L; ++l) lt[l] = tb.add(codes + (size_t)l * R, R);
+  for (int l = 0; l < c.L; ++l) {
+    lt[l] = tb.add(codes + (size_t)l * R, R);
+    if (lt[l].nA > 0) SPIDER_TRY(check_longest(c, max_s));
+  }
   SPIDER_TRY(upload_ints(tab.data(), tab.size(), ws.tables, st));
 
   PrefillRun<AT> run{c, W, h, ws, ws.tables, ws.tables, ws.tables + R, R, max_s, st};
@@ -1394,6 +1404,7 @@ spider_status run_prefill_online(const spider_decoder_cfg& c, const spider_layer
 
   std::vector<int32_t> fixed(ot.reg[0], 0);
   const int max_s = fill_positions(B, cu, fixed.data() + ot.pos, fixed.data() + ot.start);
+  SPIDER_TRY(check_longest(c, max_s));  // the text rows always query
   std::copy(cu, cu + B + 1, fixed.begin() + ot.cu);
   int nvis = 0;
   for (int b = 0; b < B; ++b)

@@ -206,6 +206,15 @@ def test_prefill_validation_before_any_hip_call(L):
     assert lib_mod.prefill_workspace_size(bf, 1, 192) > 0
 
 
+def test_fp32_samples_past_the_attention_are_refused_before_any_hip_call(L):
+    f32 = lib_mod.decoder_cfg(2, 8, 2, 16, lib_mod.F32)
+    cu = np.array([0, 3, 40964], np.int32)
+    codes = np.ones((2, 40964), np.uint8)
+    codes[1, 0] = 0
+    assert _prefill_call(L, f32, cu, codes) == UNSUPPORTED
+    assert _online_call(L, f32, cu, n_text=1) == UNSUPPORTED
+
+
 def _online_call(L, cfg, cu, n_text=4, V=32000, wu=0x1000, sel=None, tgt=None, w1=1.0, T=1.0,
                  ws_bytes=1 << 40):
     W = (lib_mod.LayerWeights * cfg.L)()
