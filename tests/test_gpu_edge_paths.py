@@ -10,7 +10,7 @@
   row tiles) and of 260, at a width outside
   the fused epilogues' tiles (partials and decode_qkv);
 * a SwiGLU width for which the streaming GEMM takes its widest column tile (288 tiles of 48
-  columns would be a second wave of blocks), over one and over all row tiles.
+  columns would be a second wave of blocks), over one, two and all row tiles.
 
 Bars as in test_gpu_prefill and test_gpu_decode; the cache-filling prefill must return the
 same bits as the plain one.
@@ -40,6 +40,7 @@ CASES = {
     "bf16_33_samples": (H, 256, 2, 320, list(range(0, 232, 7)), 4, 0.3, True),
     "bf16_260_samples": (H, 384, 3, 320, list(range(0, 781, 3)), 2, 0.3, True),
     "bf16_wide_ffn_40_rows": (H, 256, 2, 13824, [0, 40], 8, 0.3, True),
+    "bf16_wide_ffn_100_rows": (H, 256, 2, 13824, [0, 100], 8, 0.3, False),
     "bf16_wide_ffn_256_rows": (H, 256, 2, 13824, [0, 56, 256], 30, 0.1, False),
 }
 
