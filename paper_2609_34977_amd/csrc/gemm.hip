@@ -1426,13 +1426,14 @@ constexpr int kTargetBlocks = 256;
 // Split-K of the tile and LDS-staged kernels.  Tile kernel (one block per CU):
 // the largest split whose grid still fits in one wave of blocks; a second
 // partial wave costs more than it hides.  LDS-staged kernel: split until the
-// grid covers the chip.
+// grid covers the chip.  Both double, never past split_max: it need not be a power
+// of two, and the partial sums have room for that many slabs and no more.
 int choose_split(int tiles, int K, int split_max, int kgran, bool one_wave) {
   int split = 1;
   if (one_wave) {
-    while (split < split_max && tiles * split * 2 <= kTargetBlocks && K / (kgran * split * 2) >= 4) split *= 2;
+    while (2 * split <= split_max && tiles * split * 2 <= kTargetBlocks && K / (kgran * split * 2) >= 4) split *= 2;
   } else {
-    while (split < split_max && tiles * split < kTargetBlocks && K / (kgran * split * 2) >= 4) split *= 2;
+    while (2 * split <= split_max && tiles * split < kTargetBlocks && K / (kgran * split * 2) >= 4) split *= 2;
   }
   return split;
 }
