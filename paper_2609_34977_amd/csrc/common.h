@@ -216,11 +216,12 @@ __device__ __forceinline__ void dma16(const uint16_t* g, uint32_t lds) {
 // At most N of this wave's DMAs still in flight, then the block barrier: the
 // older DMAs of every wave have landed and every wave is done reading what
 // the next DMAs overwrite.  One assembly statement with a memory clobber, so
-// no LDS access moves across it.
+// no LDS access moves across it; the wait for LDS reads is part of it, because
+// the compiler may place its own behind the barrier, with the MMAs that use them.
 template <int N = 0>
 __device__ __forceinline__ void dma_wait_barrier() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
 // Every DMA of this wave complete (no barrier), as a compiler fence.

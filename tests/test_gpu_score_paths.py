@@ -73,3 +73,23 @@ def test_select_special_scores(n):
         i = np.nonzero(cl == k)[0]
         want |= set(i[np.argsort(key[i], kind="stable")][:quota[k]].tolist())
     assert sel["idx"][0, :int(sel["count"][0])].tolist() == sorted(want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("G,K", [(60, 4), (100, 8)])
+def test_tiles_of_a_large_batch_have_their_own_bits(G, K):
+    """1080 and 1800 similarity blocks, two to a CU: every tile's scores are those of the tile alone,
+    pass after pass (an LDS stage refilled while a wave still reads it shows here first)."""
+    L = need_gpu()
+    log(f"[score paths] {G} tiles of 4, K={K}")
+    cfg = ScoreCfg(G=4, n=576, H=3, d_v=1024, layers=(12, 24), feat_dtype="bf16", keep=128, K=K)
+    attn, feats = llava_taps(cfg, 9)
+    attn, feats = attn.cuda(), [f.cuda() for f in feats]
+    alone = [L.score(attn[g:g + 1], [f[g:g + 1] for f in feats], 89, K, 10) for g in range(4)]
+    of = [g % 4 for g in range(G)]
+    many = attn[of].contiguous(), [f[of].contiguous() for f in feats]
+    for _ in range(10):
+        out = L.score(*many, 89, K, 10)
+        for key in ("a", "cluster", "s", "m"):
+            want = torch.cat([alone[g][key] for g in of])
+            assert torch.equal(out[key], want), key
