@@ -1778,15 +1778,19 @@ hipError_t launch_gemm_bf16(GemmArgs& a, int split_max, hipStream_t st) {
   }
   // Shapes the tile kernel does not take (past 256 rows; K and N are multiples of
   // 64 and the outputs aligned, so the streaming kernel takes the rest)
-  const int BM = 128, BN = dual ? 64 : 128;
-  for (int i = 0; i < a.ngroups; ++i)
-    if (a.g[i].N % BN) return hipErrorInvalidValue;
+  const int BM = 128;
+  int BN = dual ? 64 : 128;
+  for (int i = 0; i < a.ngroups; ++i) {
+    if (a.g[i].N % 64) return hipErrorInvalidValue;
+    if (a.g[i].N % 128) BN = 64;  // a vocabulary of 32064, say
+  }
   if (a.K % 32) return hipErrorInvalidValue;
   a.split = dual ? 1 : choose_split(tiles_for(a, BM, BN), a.K, split_max, 32, false);
   a.k_per_split = ceil_div(a.K / 32, a.split) * 32;
   fill_tiles(a, BM, BN);
   if (a.total_tiles == 0) return hipSuccess;
   if (dual) launch_cfg<128, 64, 2, 2, true>(a, st);
+  else if (BN == 64) launch_cfg<128, 64, 2, 2, false>(a, st);
   else launch_cfg<128, 128, 2, 2, false>(a, st);
   return hipGetLastError();
 }

@@ -2,7 +2,8 @@
 // caps, and reads the split-K factor each launch chose: a launch that takes more than its
 // cap writes past the partial-sum buffer that the cap was worked out from.  Nothing is
 // launched: without a GPU the call ends in hipErrorNoDevice, its choice already made.
-// Prints one line per kernel path: path, launches, launches above one split, over the cap
+// Prints one line per kernel path: path, launches, launches above one split, over the cap;
+// then the refused shapes of widths and depths that are multiples of 64
 #include <cstdio>
 
 #include "kernels.h"
@@ -17,8 +18,8 @@ int main() {
   }
   void* p = reinterpret_cast<void*>(1 << 20);
   const char* names[] = {"few", "stream", "tile", "staged"};
-  int n[4] = {}, split[4] = {}, over[4] = {};
-  for (int N : {64, 256, 384, 512, 640, 1024, 2048, 4096, 5120, 8192})
+  int n[4] = {}, split[4] = {}, over[4] = {}, refused = 0;
+  for (int N : {64, 192, 256, 384, 512, 640, 1024, 2048, 4096, 5120, 8192})
     for (int K : {32, 64, 96, 512, 1024, 2048, 4096, 5120, 5504, 11008, 13824})
       for (int cap = 1; cap <= 8; ++cap)
         for (int M = 1; M <= 4200; M += M < 300 ? 1 : 37) {
@@ -30,12 +31,16 @@ int main() {
           a.split = 0;
           const hipError_t e = launch_gemm_bf16(a, cap, nullptr);
           (void)hipGetLastError();
-          if (e == hipErrorInvalidValue) continue;  // a shape no kernel takes
+          if (e == hipErrorInvalidValue) {  // a shape no kernel takes
+            refused += N % 64 == 0 && K % 64 == 0;
+            continue;
+          }
           const int path = M <= 4 ? 0 : (M <= 256 ? 1 : (N % 256 == 0 && K % 64 == 0 ? 2 : 3));
           ++n[path];
           split[path] += a.split > 1;
           over[path] += a.split > cap || a.split < 1;
         }
   for (int i = 0; i < 4; ++i) printf("%s %d %d %d\n", names[i], n[i], split[i], over[i]);
+  printf("refused %d\n", refused);
   return 0;
 }

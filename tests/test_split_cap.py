@@ -1,4 +1,5 @@
-"""No GEMM launch takes more split-K slabs than its cap, whatever the cap.
+"""No GEMM launch takes more split-K slabs than its cap, whatever the cap, and every width and
+depth that the callers accept (multiples of 64) is taken at every row count.
 
 The caller works the cap out from the rows its partial-sum buffer holds, so it is any number
 from 1 to 8.  tests/native/split_cap.cpp reads the choice of the library's own host code
@@ -26,6 +27,7 @@ def test_no_launch_splits_past_its_cap(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
     table = {p: tuple(int(x) for x in v) for p, *v in (line.split() for line in r.stdout.splitlines())}
+    assert table.pop("refused") == (0,), "widths and depths of multiples of 64 are accepted"
     assert set(table) == {"few", "stream", "tile", "staged"}
     for path, (launches, split, over) in table.items():
         assert launches > 1000 and over == 0, table
