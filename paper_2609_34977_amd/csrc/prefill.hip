@@ -430,12 +430,11 @@ __device__ __forceinline__ void unpack16(const uint4& v, float* x) {
 }
 
 // grid (H, B): one query (the new token) against the cache rows 0..lens[b].
-// Logits fp32: where a row is a power of two of 16-byte vectors (at most 64), a
-// lane per vector and a butterfly over the row's lanes, else a thread per key and
-// c ascending.  Softmax with the block max, exponentials summed per thread in key
-// order then in a fixed tree.  P.V in fp32: a thread per (vector of VE columns,
-// key group g of G = 256 / (vectors per row)) sums keys g, g + G, ..., the G
-// partial sums are added in order, one division.
+// Logits fp32: by rows (a lane per 16-byte vector, a butterfly over the row's
+// lanes) or a thread per key and c ascending, see by_rows.  Softmax with the block
+// max, exponentials summed per thread in key order then in a fixed tree.  P.V in
+// fp32: a thread per (vector of VE columns, key group g of G = 256 / (vectors per
+// row)) sums keys g, g + G, ..., the G partial sums are added in order, one division.
 template <typename AT>
 __global__ void __launch_bounds__(256) decode_attention_kernel(const AT* __restrict__ Q, const AT* __restrict__ ck,
                                                                const AT* __restrict__ cv, int64_t layer_off, int cap,
@@ -455,20 +454,34 @@ __global__ void __launch_bounds__(256) decode_attention_kernel(const AT* __restr
   const AT* kb = ck + layer_off + (int64_t)b * cap * d + h * dh;
   const AT* vb = cv + layer_off + (int64_t)b * cap * d + h * dh;
   // P V work split (below); this thread's first PF value vectors are loaded
-  // now, so their latency overlaps the scores and the softmax
+  // now, so their latency overlaps the scores and the softmax (clamped to the last
+  // key instead of under a check they cost bf16 of 128 10 to 15 % from 1500 keys on)
   constexpr int PF = 16;
   const int ng = 256 / nv;  // key groups
   const int cg = tid % nv, kg = tid / nv;
   uint4 vpre[PF];
 #pragma unroll
-  for (int u = 0; u < PF; ++u)
-    vpre[u] = reinterpret_cast<const uint4*>(vb + (int64_t)min(kg + u * ng, n - 1) * d)[cg];
+  for (int u = 0; u < PF; ++u) {
+    const int j = kg + u * ng;
+    vpre[u] = (kg < ng && j < n) ? reinterpret_cast<const uint4*>(vb + (int64_t)j * d)[cg] : make_uint4(0, 0, 0, 0);
+  }
   float mx = -INFINITY;
-  if ((nv & (nv - 1)) == 0 && nv <= 64) {
-    // Scores: the nv lanes that hold a key's row between them (a whole row per
-    // group: coalesced, eight rows in flight), their partial sums added by a
-    // butterfly.  A thread per key instead reads a row's vectors one by one
-    // from its own line (8 samples of 40 heads and 280 keys: 23 us, 18 now).
+  // Scores, two ways.  By rows: the nv lanes that hold a key's row between them (a
+  // whole row per group: coalesced, eight rows in flight), their partial sums added
+  // by a butterfly (DPP for 16 lanes, LDS shuffles else).  By keys: a thread per key
+  // reads its row's vectors, 256 rows in flight.  Up to a block per CU the length of
+  // the chain counts, beyond that the lines read.  Measured by rows / by keys, us.
+  // bf16 of 128: 32 blocks, 800 keys 20 / 21, 3000 66 / 63, 8000 167 / 149; 128 blocks,
+  // 1500 keys 36 / 38, 4100 93 / 88; 256 blocks, 3000 keys 91 / 103; 288 blocks, 800
+  // keys 27 / 37.  fp32 of 64: 4 blocks, 3000 keys 47 / 47, 8000 142 / 134; 256 blocks,
+  // 4100 keys 113 / 140.  fp32 of 128: 256 blocks, 800 keys 71 / 55; 288 blocks, 100
+  // keys 16 / 14, 800 74 / 83.  fp32 of 32: 256 blocks, 800 keys 20 / 18; 288 blocks,
+  // 100 keys 9.1 / 8.6, 800 22 / 23.  fp32 of 256: 256 blocks, 800 keys 146 / 98; 272
+  // blocks 149 / 152.
+  const int blocks = gridDim.x * gridDim.y;
+  const bool by_rows = nv == 16 ? blocks >= 256 || n <= 2048
+                                : blocks > 256 && n >= 256 && (nv == 8 || nv == 32 || nv == 64);
+  if (by_rows) {
     float qv[VE];
 #pragma unroll
     for (int e = 0; e < VE; ++e) qv[e] = qs[cg * VE + e];
